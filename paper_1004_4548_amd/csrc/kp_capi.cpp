@@ -303,6 +303,12 @@ struct Plan {
   int64_t rnr = 0, rnsplit = 1, rrows = 0, rbins = 0, rnbk = 0, rsplit_cap = 1;
   int rshift = 0;
   int64_t rtarget = 1;
+  // straight from the sorted factors: rows are B's terms (swap), cells of
+  // 2^dcw codes, products per interval, intervals, buckets of rows and columns
+  bool direct = false, dswap = false, dsmall = false, dwide = false;
+  int dcw = 0, dshift[2] = {0, 0};
+  int64_t dncell = 0, dtarget = 1, dunits = 0;
+  int64_t dmax[2] = {0, 0}, dnbk[2] = {0, 0};
 };
 
 // Truncation tables: slack of A's terms and degree of B's (input order),
@@ -462,6 +468,15 @@ struct RangeCarve {
   void* ent;
 };
 
+// Arrays of the accumulation straight from the sorted factors.
+struct DirectCarve {
+  int64_t* ccount;
+  longlong2* units;
+  struct {
+    int32_t* rank; int32_t* start; int64_t* k64; uint32_t* k32; uint64_t* c; uint4* px;
+  } set[2];   // rows, columns
+};
+
 struct HashCarve {
   Meta* meta;
   RangeCarve rg;
@@ -531,6 +546,121 @@ void range_shape(const kp_layout* L, int64_t na, int64_t nb, int64_t nprod, int 
   const int64_t maxB = factor_maxcode(L, 1);
   p->rshift = dense_bucket_shift(maxB, nb);
   p->rnbk = (maxB >> p->rshift) + 1;
+}
+
+// Shape of the accumulation straight from the sorted factors; false when the
+// product is outside what its kernels take, or better in groups:
+// every interval looks at every row that meets it, so that the rows (the
+// factor of fewer terms) may be at most DIRECT_ROWS.
+bool direct_shape(const kp_ctx* ctx, const kp_layout* L, int64_t na, int64_t nb, Plan* p) {
+  const int64_t pairs = sat_mul(na, nb);
+  if (pairs < 1 || pairs > ((int64_t)1 << 32)) return false;
+  p->dswap = na > nb;
+  const int64_t n[2] = {p->dswap ? nb : na, p->dswap ? na : nb};
+  if (n[0] > DIRECT_ROWS || n[1] > ((int64_t)1 << 24)) return false;
+  for (int k = 0; k < 2; ++k) {
+    p->dmax[k] = factor_maxcode(L, p->dswap ? 1 - k : k);
+    p->dshift[k] = dense_bucket_shift(p->dmax[k], n[k]);
+  }
+  // small intervals while looking at their rows is cheap
+  p->dsmall = n[0] <= DIRECT_SMALL_ROWS;
+  const int64_t full = p->dsmall ? DIRECT_SMALL_PRODUCTS : DIRECT_PRODUCTS;
+  int K = 0;
+  while (K < 62 && ((int64_t)1 << K) < L->nkeys) ++K;
+  int lc = 6;   // cells of about 2^15 products
+  while (lc < 13 && ((int64_t)1 << (lc + 15)) < pairs) ++lc;
+  // Cells of at most 2^31 codes, so that offsets are 32-bit (the columns'
+  // buckets are then at most 2^30 codes wide), unless such cells are too many
+  // or would hold less than a quarter of an interval's products each.
+  const int need = std::max(0, K - 31);
+  p->dwide = need > 14 || (need > lc && (pairs >> need) < full / 4) ||
+             (p->dmax[1] >> 30) >= DENSE_MAX_BUCKETS;
+  if (!p->dwide) {
+    lc = std::max(lc, need);
+    p->dshift[1] = std::min(p->dshift[1], 30);
+  }
+  p->dcw = std::max(0, K - lc);
+  p->dncell = (L->nkeys + ((int64_t)1 << p->dcw) - 1) >> p->dcw;
+  for (int k = 0; k < 2; ++k) p->dnbk[k] = (p->dmax[k] >> p->dshift[k]) + 1;
+  // small products: enough intervals for two rounds of workgroups
+  const int64_t wgs = (p->dsmall ? 4 : 1) * (int64_t)ctx->num_cu;
+  p->dtarget = std::min(full, std::max<int64_t>(256, pairs / (2 * wgs)));
+  p->dunits = p->dncell + (pairs + pairs / 2) / p->dtarget + 64;
+  return p->dunits < ((int64_t)1 << 31);
+}
+
+void carve_direct(Carver& c, const Plan& p, int64_t na, int64_t nb, DirectCarve* d) {
+  *d = DirectCarve{};
+  d->ccount = c.take<int64_t>(p.dncell);
+  d->units = c.take<longlong2>(p.dunits);
+  for (int k = 0; k < 2; ++k) {
+    const int64_t n = (k == 0) != p.dswap ? na : nb;
+    auto& s = d->set[k];
+    s.rank = c.take<int32_t>(n);
+    s.start = c.take<int32_t>(p.dnbk[k] + 1);
+    s.k64 = k == 0 || p.dwide ? c.take<int64_t>(n) : nullptr;
+    s.k32 = k == 1 && !p.dwide ? c.take<uint32_t>(n) : nullptr;
+    s.c = c.take<uint64_t>(n);
+    s.px = c.take<uint4>(n);
+  }
+}
+
+// The kernel arguments of a planned product; the caller adds the outputs.
+DirectArgs direct_args(const Plan& p, kp_dtype dt, const kp_layout* L, const DirectCarve& d,
+                       Meta* meta, const int64_t* a_codes, const void* a_coef, int64_t na,
+                       const int64_t* b_codes, const void* b_coef, int64_t nb) {
+  DirectArgs R{};
+  R.meta = meta;
+  R.f64 = dt == KP_F64 ? 1 : 0;
+  R.wide = dt == KP_I128 ? 1 : 0;
+  R.ncodes = L->nkeys;
+  R.cw = p.dcw;
+  R.ncell = p.dncell;
+  R.ccount = d.ccount;
+  R.target = p.dtarget;
+  R.small = p.dsmall ? 1 : 0;
+  R.wide_codes = p.dwide ? 1 : 0;
+  R.max_units = p.dunits;
+  R.units = d.units;
+  for (int k = 0; k < 2; ++k) {
+    const bool isb = (k == 1) != p.dswap;
+    DirectSet& s = R.set[k];
+    s.k_in = isb ? b_codes : a_codes;
+    s.c_in = static_cast<const uint64_t*>(isb ? b_coef : a_coef);
+    s.n = isb ? nb : na;
+    s.maxc = p.dmax[k];
+    s.shift = p.dshift[k];
+    s.nbk = p.dnbk[k];
+    s.rank = d.set[k].rank;
+    s.start = d.set[k].start;
+    s.k64 = d.set[k].k64;
+    s.k32 = d.set[k].k32;
+    s.c = d.set[k].c;
+    s.px = d.set[k].px;
+  }
+  return R;
+}
+
+// Decoded output: the digits whose product leaves 32-bit arithmetic room (an
+// offset is below 2^31 and an interval's low part below that product), and how
+// a term's digits pack into 128 bits: sixteen of a byte or eight of two bytes.
+void direct_digits(DirectArgs* R, const kp_layout& L) {
+  uint64_t d = 1, most = 0;
+  bool low = true;
+  R->ndig = L.nx;
+  R->nlow = 0;
+  for (int k = 0; k < L.nx; ++k) {
+    const uint64_t w = (uint64_t)L.xw[k];
+    most = std::max(most, w);
+    low = low && w <= ((uint64_t)1 << 31) / d;
+    if (low) {
+      d *= w;
+      R->nlow = k + 1;
+    }
+  }
+  R->div_low64 = make_fastdiv(d);
+  R->div_low = make_fastdiv32(d);
+  R->field = most <= 256 && L.nx <= 16 ? 1 : most <= 65536 && L.nx <= 8 ? 2 : 0;
 }
 
 void carve_hash(Carver& c, const Plan& p, int poisson, int64_t na, int64_t nb, HashCarve* h) {
@@ -748,6 +878,21 @@ kp_status make_plan(kp_ctx* ctx, const kp_layout* L, int poisson, kp_dtype dt, k
     }
     HashCarve h;
     carve_hash(c, *p, poisson, na, nb, &h);
+    // Straight from the sorted factors for products spread thinly over the
+    // code space, unless a knob asks for a grouped layout; the workspace stays
+    // the grouped layout's, which is larger.
+    const kp_tune& t = ctx->tune;
+    const bool plain = t.hash_partitioned == 1 && t.hash_grouping == 0 &&
+                       t.hash_bin_slots == 4096 && t.hash_max_bin_bits == 10 &&
+                       t.hash_bin_fill == 42;
+    if (!poisson && (p->radix || p->range) && plain && !p->trunc && thin &&
+        direct_shape(ctx, L, na, nb, p)) {
+      Carver k;
+      (void)k.take<Meta>(1);
+      DirectCarve d;
+      carve_direct(k, *p, na, nb, &d);
+      p->direct = k.off <= c.off;
+    }
   }
   TruncBufs tb;
   carve_trunc(c, *p, na, nb, &tb);
@@ -843,6 +988,7 @@ kp_status kp_ctx_create(int device, kp_ctx** out) {
   if (e == hipSuccess) e = hipMemset(ctx->status, 0, sizeof(CtxStatus));
   if (e == hipSuccess) e = dense_setup();
   if (e == hipSuccess) e = range_setup();
+  if (e == hipSuccess) e = direct_setup();
   if (e == hipSuccess)
     e = hipHostMalloc(reinterpret_cast<void**>(&ctx->mb), sizeof(Mailbox),
                       hipHostMallocCoherent | hipHostMallocMapped);
@@ -1232,6 +1378,32 @@ kp_status enqueue_laurent(kp_ctx* ctx, const kp_layout* layout, kp_dtype dtype, 
     H.a_sa = tr.sa;
     H.b_tb = tr.tb;
     if (!empty && timed) std::tie(H.ev0, H.ev1) = timing_pair(ctx);
+    if (!empty && p.direct) {
+      Carver k;
+      k.base = static_cast<char*>(workspace);
+      Meta* meta = k.take<Meta>(1);
+      DirectCarve d;
+      carve_direct(k, p, na, nb, &d);
+      DirectArgs R = direct_args(p, dtype, layout, d, meta, a_codes, a_coef, na, b_codes, b_coef,
+                                 nb);
+      R.out_k = out_codes;
+      R.out_c = out_coef;
+      R.out_cap = out_cap;
+      if (xo) {
+        R.out_x = xo->exps;
+        R.dec = xo->dec;
+        direct_digits(&R, *layout);
+        xo->decoded = true;
+        xo->posted = xo->seq != 0;
+      }
+      R.ev0 = H.ev0;
+      R.ev1 = H.ev1;
+      R.stats = H.stats;
+      e = launch_direct(R, dtype, out_n, &ctx->status->err, xo && xo->seq ? xo->mb : nullptr,
+                        xo ? xo->seq : 0, stream);
+      if (e != hipSuccess) return hip_fail(ctx, e, "kp_mul_laurent launch");
+      return KP_OK;
+    }
     e = launch_meta_init(h.meta, stream);
     if (!empty && p.range) {
       const RangeCarve& g = h.rg;

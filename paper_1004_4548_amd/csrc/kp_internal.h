@@ -239,6 +239,11 @@ struct Meta {
   int64_t entries;        // products written (grouped entries)
   uint32_t pack;          // entries packed in 8 bytes (value above the hash bits)
   uint32_t reserve;       // each range's terms go to its own entry slots (no shared counter)
+  // hash accumulation from sorted factors: error bits of each set, least and
+  // largest size of its coefficients, whether a product can be zero
+  uint32_t set_err[2];
+  unsigned long long set_min[2], set_max[2];
+  uint32_t zeros;
 };
 
 // Status block owned by a context (device memory, 256 bytes).
@@ -551,6 +556,65 @@ struct RangeArgs {
 };
 hipError_t range_setup();
 hipError_t launch_range(const RangeArgs& R, kp_dtype dt, hipStream_t s);
+
+// Hash accumulation straight from the sorted factors (kp_direct.hip): each
+// workgroup takes an interval of output codes, finds its products from the
+// rows (the factor of fewer terms) and intervals of the columns, and adds them
+// in an LDS table.
+// Hash cells (two bits each) of an interval of large and of small intervals,
+// and products wanted in them: one cell in eleven is marked, so that one
+// product in eleven shares its cell by chance and goes through the table.
+constexpr int DIRECT_CELLS_LOG = 18, DIRECT_SMALL_CELLS_LOG = 16;
+constexpr int64_t DIRECT_PRODUCTS = (1 << DIRECT_CELLS_LOG) / 11;
+constexpr int64_t DIRECT_SMALL_PRODUCTS = (1 << DIRECT_SMALL_CELLS_LOG) / 11;
+// Rows up to which every interval may look at every row.  Measured against the
+// range-grouped layout, int64, six variables in [0, 80]: 20,000 x 20,000 terms
+// 8.6 ms against 11.0, 30,000 x 30,000 terms 27.9 ms against 23.7.
+constexpr int64_t DIRECT_ROWS = 24000;
+// Rows up to which small intervals win: 200 x 20,000 terms 0.23 ms against
+// 0.41 with large ones, 1,000 x 20,000 0.39 against 0.53, 3,000 x 3,000 0.33
+// against 0.27.
+constexpr int64_t DIRECT_SMALL_ROWS = 2048;
+constexpr int64_t DIRECT_PLACE = 4096;  // larger sets are placed by a launch of their own
+// A factor's terms by bucket of their code.
+struct DirectSet {
+  const int64_t* k_in; const uint64_t* c_in;
+  int64_t n, maxc;               // terms, largest code
+  int32_t shift;                 // buckets of 2^shift codes
+  int64_t nbk;
+  int32_t* rank; int32_t* start; // [n], [nbk + 1]
+  int64_t* k64; uint32_t* k32;   // sorted codes, low words of the columns' codes
+  uint64_t* c;                   // coefficients
+  uint4* px;                     // digits, in fields of DirectArgs::field bytes
+};
+struct DirectArgs {
+  Meta* meta;
+  DirectSet set[2];              // rows (the factor of fewer terms), columns
+  int32_t f64, wide;             // fp64 coefficients; 128-bit products
+  int64_t ncodes;                // codes of the product
+  int32_t cw;
+  int64_t ncell;                 // cells of 2^cw codes
+  int64_t* ccount;               // [ncell] products (bound)
+  int64_t target, max_units;     // products per interval, intervals at most
+  int32_t small;                 // small intervals (DIRECT_SMALL_PRODUCTS)
+  int32_t wide_codes;            // cells of more than 2^31 codes: 64-bit offsets
+  longlong2* units;              // [max_units] {first code, codes}
+  int64_t* out_k; void* out_c; int64_t out_cap;
+  int32_t* out_x;                // optional decoded output
+  DevLayout dec;
+  // decoded output: ndig digits, the first nlow of which have a product
+  // (div_low) that leaves 32-bit arithmetic room
+  int32_t ndig, nlow;
+  int32_t field;                 // bytes of a packed digit (1 or 2; 0: not packed)
+  FastDiv div_low64;
+  FastDiv32 div_low;
+  unsigned long long* stats;
+  hipEvent_t ev0, ev1;
+};
+hipError_t direct_setup();
+// mb: the count is posted there under seq (null: not).
+hipError_t launch_direct(const DirectArgs& R, kp_dtype dt, int64_t* out_n, uint32_t* ctx_err,
+                         Mailbox* mb, uint64_t seq, hipStream_t s);
 
 // packed batches (kp_pack.hip): many whole Laurent products in one fixed
 // sequence of persistent launches that read a device task table
