@@ -505,16 +505,15 @@ kp_status kp_batch_status(kp_batch* batch, int64_t task_id, int64_t* n_out);
  * schoolbook sum of Section 3 over the Kronecker codes of Section 2, the same
  * set of terms as kp_mul_laurent_exps gives).  The products' descriptions sit
  * in a device task table; each stage is one launch of a fixed grid whose
- * workgroups walk the work of every task (encode both factors and clear the
- * accumulator; form every pair's product and add it at its code; compact the
- * nonzero sums, decoding them to exponents; post the counts).  Each product
- * accumulates in device memory of its own: one word per code when the key
- * space is at most twice the size of the hash table it would otherwise get
- * (Section 3.1's dense array), else an open-addressing hash table of at least
- * twice the result bound, compare-and-swap on the key and atomic add on the
- * coefficient (Section 3.2).  Meant for many small products, whose cost per
- * call is launches and host waits; large products are better served one call
- * each.
+ * workgroups walk the work of every task (encode both factors and sort them by
+ * code; bound the products of intervals of output codes; form each interval's
+ * products and add them in the workgroup's LDS, writing the nonzero sums
+ * decoded to exponents; post the counts).  An interval no wider than the LDS
+ * table is indexed by code (Section 3.1's dense array), a wider one is an
+ * open-addressing hash table, compare-and-swap on the key and atomic add on
+ * the coefficient (Section 3.2).  Meant for many small products, whose cost
+ * per call is launches and host waits; large products are better served one
+ * call each.
  *
  * kp_pack_create: a pack for up to max_tasks (1..4096) products; it owns a
  *   device task table and pinned host memory for the boxes and counts.
@@ -528,7 +527,7 @@ kp_status kp_batch_status(kp_batch* batch, int64_t task_id, int64_t* n_out);
  *   go to out_exps[k] (int32 [out_cap[k]][nvars]) and out_coef[k]
  *   ([out_cap[k]], the task's type), in unspecified order.  `arena` is
  *   caller-owned device memory of at least *arena_bytes.  With KP_PACK_GRAPH
- *   the upload of the table and the four launches are captured into a HIP
+ *   the upload of the table and the five launches are captured into a HIP
  *   graph at the first such run and replayed by every later one (any
  *   products: the kernels read them from the table); capture needs a stream
  *   other than the null stream.

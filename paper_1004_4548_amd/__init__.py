@@ -906,14 +906,10 @@ class Pack:
             X = new(max(nx, 1), torch.int32)
             V = new(max(sum(caps), 1), torch.int64)
             arena = new(max(ab, 256), torch.uint8)
-        ox, oc, views, px, pc = (C.c_void_p * max(n, 1))(), (C.c_void_p * max(n, 1))(), [], 0, 0
+        ox, oc, px, pc = (C.c_void_p * max(n, 1))(), (C.c_void_p * max(n, 1))(), 0, 0
+        x0, v0 = X.data_ptr(), V.data_ptr()
         for k, (a, _) in enumerate(products):
-            x = X[px:px + caps[k] * a.nv].view(caps[k], a.nv)
-            v = V[pc:pc + caps[k]]
-            if a.coef.dtype == torch.float64:
-                v = v.view(torch.float64)
-            ox[k], oc[k] = x.data_ptr(), v.data_ptr()
-            views.append((x, v))
+            ox[k], oc[k] = x0 + 4 * px, v0 + 8 * pc
             px += caps[k] * a.nv
             pc += caps[k]
         self.ctx.check(lib().kp_pack_run(self.h, ox, oc, C.c_void_p(arena.data_ptr()), ab,
@@ -921,6 +917,14 @@ class Pack:
                                          C.c_void_p(run_on.cuda_stream)))
         if run_on is not cur:
             cur.wait_stream(run_on)
+        # the views are made while the products run
+        views, px, pc = [], 0, 0
+        for k, (a, _) in enumerate(products):
+            x = X[px:px + caps[k] * a.nv].view(caps[k], a.nv)
+            v = V[pc:pc + caps[k]]
+            views.append((x, v.view(torch.float64) if a.coef.dtype == torch.float64 else v))
+            px += caps[k] * a.nv
+            pc += caps[k]
         self._planned = None
         self._run = (products, views, arena, n)
 

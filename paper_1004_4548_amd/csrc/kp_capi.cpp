@@ -307,7 +307,7 @@ struct Plan {
   // 2^dcw codes, products per interval, intervals, buckets of rows and columns
   bool direct = false, dswap = false, dsmall = false, dwide = false;
   int dcw = 0, dshift[2] = {0, 0};
-  int64_t dncell = 0, dtarget = 1, dunits = 0;
+  int64_t dncell = 0, dtarget = 1, dunits = 0, dgrid = 0, dncrowd = 0;
   int64_t dmax[2] = {0, 0}, dnbk[2] = {0, 0};
 };
 
@@ -472,6 +472,7 @@ struct RangeCarve {
 struct DirectCarve {
   int64_t* ccount;
   longlong2* units;
+  int64_t* bounds; int64_t* tmp_k; int32_t* tmp_i;   // crowded columns
   struct {
     int32_t* rank; int32_t* start; int64_t* k64; uint32_t* k32; uint64_t* c; uint4* px;
   } set[2];   // rows, columns
@@ -557,7 +558,7 @@ bool direct_shape(const kp_ctx* ctx, const kp_layout* L, int64_t na, int64_t nb,
   if (pairs < 1 || pairs > ((int64_t)1 << 32)) return false;
   p->dswap = na > nb;
   const int64_t n[2] = {p->dswap ? nb : na, p->dswap ? na : nb};
-  if (n[0] > DIRECT_ROWS || n[1] > ((int64_t)1 << 24)) return false;
+  if (n[0] > DIRECT_ROWS || n[1] > DIRECT_COLUMNS) return false;
   for (int k = 0; k < 2; ++k) {
     p->dmax[k] = factor_maxcode(L, p->dswap ? 1 - k : k);
     p->dshift[k] = dense_bucket_shift(p->dmax[k], n[k]);
@@ -585,13 +586,22 @@ bool direct_shape(const kp_ctx* ctx, const kp_layout* L, int64_t na, int64_t nb,
   // small products: enough intervals for two rounds of workgroups
   const int64_t wgs = (p->dsmall ? 4 : 1) * (int64_t)ctx->num_cu;
   p->dtarget = std::min(full, std::max<int64_t>(256, pairs / (2 * wgs)));
-  p->dunits = p->dncell + (pairs + pairs / 2) / p->dtarget + 64;
+  p->dgrid = p->dncell + (pairs + pairs / 2) / p->dtarget + 64;
+  // crowded columns: sampled cells of up to a quarter of an interval, which 32-bit offsets
+  // may cut once more per 2^31 codes (at most once per cell of equal width)
+  p->dncrowd = 64;
+  const int64_t held = std::min(p->dtarget, full / 4);
+  while (p->dncrowd < DIRECT_CROWD_CELLS && p->dncrowd * held < pairs) p->dncrowd *= 2;
+  p->dunits = p->dgrid + p->dncrowd + p->dncell;
   return p->dunits < ((int64_t)1 << 31);
 }
 
 void carve_direct(Carver& c, const Plan& p, int64_t na, int64_t nb, DirectCarve* d) {
   *d = DirectCarve{};
-  d->ccount = c.take<int64_t>(p.dncell);
+  d->ccount = c.take<int64_t>(std::max(p.dncell, p.dncrowd));
+  d->bounds = c.take<int64_t>(p.dncrowd + 1);
+  d->tmp_k = c.take<int64_t>(p.dswap ? na : nb);
+  d->tmp_i = c.take<int32_t>(p.dswap ? na : nb);
   d->units = c.take<longlong2>(p.dunits);
   for (int k = 0; k < 2; ++k) {
     const int64_t n = (k == 0) != p.dswap ? na : nb;
@@ -621,6 +631,11 @@ DirectArgs direct_args(const Plan& p, kp_dtype dt, const kp_layout* L, const Dir
   R.small = p.dsmall ? 1 : 0;
   R.wide_codes = p.dwide ? 1 : 0;
   R.max_units = p.dunits;
+  R.grid = p.dgrid;
+  R.ncrowd = (int32_t)p.dncrowd;
+  R.bounds = d.bounds;
+  R.tmp_k = d.tmp_k;
+  R.tmp_i = d.tmp_i;
   R.units = d.units;
   for (int k = 0; k < 2; ++k) {
     const bool isb = (k == 1) != p.dswap;
@@ -989,6 +1004,7 @@ kp_status kp_ctx_create(int device, kp_ctx** out) {
   if (e == hipSuccess) e = dense_setup();
   if (e == hipSuccess) e = range_setup();
   if (e == hipSuccess) e = direct_setup();
+  if (e == hipSuccess) e = pack_setup();
   if (e == hipSuccess)
     e = hipHostMalloc(reinterpret_cast<void**>(&ctx->mb), sizeof(Mailbox),
                       hipHostMallocCoherent | hipHostMallocMapped);
@@ -2065,9 +2081,8 @@ struct kp_pack {
   // the planned batch
   std::vector<kp_pack_task> tasks;
   std::vector<kp_layout> layouts;
-  std::vector<int64_t> caps, slots, off;
-  std::vector<int32_t> direct;
-  size_t arena = 0;
+  std::vector<int64_t> caps, off;
+  size_t arena = 0, units_off = 0;   // arena bytes, where the intervals lie
   bool running = false;
   hipStream_t run_stream = nullptr;
   hipGraph_t graph = nullptr;
@@ -2089,6 +2104,65 @@ void pack_free(kp_pack* p) {
   if (p->post) (void)hipHostFree(p->post);
   if (p->box_vals) (void)hipHostFree(p->box_vals);
   delete p;
+}
+
+// A task's shape and its arrays in the arena (T may be null: sizes only);
+// returns the intervals it may have.
+int64_t pack_task(kp::Carver& c, const kp_pack_task& t, const kp_layout& L, int64_t bound,
+                  kp::PackTask* T) {
+  using namespace kp;
+  const bool live = bound > 0;   // an empty product has nothing to sort
+  const bool swap = t.na > t.nb;
+  PackSet set[2];
+  for (int k = 0; k < 2; ++k) {
+    const bool isb = (k == 1) != swap;
+    PackSet& s = set[k];
+    s.n = live ? (isb ? t.nb : t.na) : 0;
+    s.maxc = live ? factor_maxcode(&L, isb) : 0;
+    // about two buckets a term
+    const int64_t want = std::min<int64_t>(PACK_BUCKETS, std::max<int64_t>(64, 2 * s.n));
+    s.shift = 0;
+    while ((s.maxc >> s.shift) + 1 > want) ++s.shift;
+    s.nbk = (int32_t)((s.maxc >> s.shift) + 1);
+    s.rank = c.take<int32_t>((size_t)s.n);
+    s.start = c.take<int32_t>((size_t)s.nbk + 1);
+    s.k = c.take<int64_t>((size_t)s.n);
+    s.c = c.take<uint64_t>((size_t)s.n);
+  }
+  // cells of about a hashed interval
+  const int64_t pairs = live ? sat_mul(t.na, t.nb) : 0;
+  int K = 0, lc = 0;
+  while (K < 62 && ((int64_t)1 << K) < L.nkeys) ++K;
+  while (((int64_t)1 << lc) < PACK_CELLS && ((int64_t)PACK_HASHED << lc) < pairs) ++lc;
+  const int cw = std::max(0, K - lc);
+  const int64_t ncell = live ? (L.nkeys + ((int64_t)1 << cw) - 1) >> cw : 0;
+  // crowded columns: cells of half a hashed interval, sampled as they are
+  int32_t ncrowd = PACK_CELLS;
+  while (ncrowd < PACK_CROWD_CELLS && (int64_t)ncrowd * (PACK_HASHED / 2) < pairs) ncrowd *= 2;
+  const int64_t max_units = live ? ncrowd + pairs / (PACK_HASHED / 2) + 16 : 0;
+  unsigned long long* cells = c.take<unsigned long long>(live ? (size_t)ncrowd : 0);
+  uint32_t* crowd = c.take<uint32_t>(1);
+  int64_t* bounds = c.take<int64_t>(live ? (size_t)ncrowd + 1 : 0);
+  int64_t* tmp_k = c.take<int64_t>((size_t)set[1].n);
+  int32_t* tmp_i = c.take<int32_t>((size_t)set[1].n);
+  unsigned long long* count = c.take<unsigned long long>(1);
+  if (T) {
+    T->set[0] = set[0];
+    T->set[1] = set[1];
+    T->nkeys = L.nkeys;
+    T->swap = swap ? 1 : 0;
+    T->cw = cw;
+    T->ncell = (int32_t)ncell;
+    T->cells = cells;
+    T->max_units = max_units;
+    T->crowd = crowd;
+    T->ncrowd = ncrowd;
+    T->bounds = bounds;
+    T->tmp_k = tmp_k;
+    T->tmp_i = tmp_i;
+    T->count = count;
+  }
+  return max_units;
 }
 
 // Waits until every word of post[0..n) carries `tag` in its high half.
@@ -2177,8 +2251,6 @@ kp_status kp_pack_plan(kp_pack* p, const kp_pack_task* tasks, int32_t n, int64_t
   p->tasks.assign(tasks, tasks + n);
   p->layouts.assign((size_t)n, kp_layout{});
   p->caps.assign((size_t)n, 0);
-  p->slots.assign((size_t)n, 0);
-  p->direct.assign((size_t)n, 0);
   p->off.assign((size_t)n, 0);
   p->arena = 0;
   // every factor's box: one launch, one wait
@@ -2201,6 +2273,7 @@ kp_status kp_pack_plan(kp_pack* p, const kp_pack_task* tasks, int32_t n, int64_t
   (void)hipSetDevice(prev);
   if (e != hipSuccess) return hip_fail(ctx, e, "kp_pack_plan boxes");
   size_t arena = 0;
+  int64_t units = 0;
   for (int32_t k = 0; k < n; ++k) {
     const kp_pack_task& t = tasks[k];
     int32_t box[2][2 * KP_MAX_VARS];
@@ -2225,22 +2298,17 @@ kp_status kp_pack_plan(kp_pack* p, const kp_pack_task* tasks, int32_t n, int64_t
                                      box[1] + KP_MAX_VARS, nullptr, nullptr, &L);
     if (st != KP_OK)
       return fail(ctx, st, "kp_pack_plan: task %d: the product's codes overflow", (int)k);
-    // bound on result terms; a hash table of at least twice as many slots, or
-    // one word per code when that is no larger
-    const int64_t pairs = t.na * t.nb;
-    const int64_t bound = L.nkeys <= 0 ? 0 : std::min<int64_t>(L.nkeys, pairs);
-    int64_t hs = 64;
-    while (hs < 2 * bound) hs <<= 1;
-    const bool dir = L.nkeys > 0 && L.nkeys <= 2 * hs;
+    const int64_t bound = L.nkeys <= 0 ? 0 : std::min<int64_t>(L.nkeys, sat_mul(t.na, t.nb));
     p->caps[(size_t)k] = bound;
-    p->slots[(size_t)k] = bound == 0 ? 0 : (dir ? L.nkeys : hs);
-    p->direct[(size_t)k] = dir ? 1 : 0;
     p->off[(size_t)k] = (int64_t)arena;
-    const int64_t words = p->direct[(size_t)k] ? p->slots[(size_t)k] : 2 * p->slots[(size_t)k];
-    arena += align_up(8 * (size_t)t.na) + align_up(8 * (size_t)t.nb) +
-             align_up(8 * (size_t)std::max<int64_t>(words, 1)) + ALIGN;
+    Carver c;
+    c.off = arena;
+    units += pack_task(c, t, L, bound, nullptr);
+    arena = c.off;
     out_cap[k] = bound;
   }
+  p->units_off = arena;
+  arena += align_up(sizeof(PackUnit) * (size_t)std::max<int64_t>(units, 1));
   p->arena = arena;
   *arena_bytes = arena;
   return KP_OK;
@@ -2261,14 +2329,10 @@ kp_status kp_pack_run(kp_pack* p, int32_t* const* out_exps, void* const* out_coe
       return fail(ctx, KP_E_ARG, "kp_pack_run: task %d has no output arrays", k);
   if ((flags & KP_PACK_GRAPH) && !stream)
     return fail(ctx, KP_E_ARG, "graph capture needs a stream other than the null stream");
-  // the table: header, unit prefixes, tasks
+  // the table: header, tasks
   const int m = p->max_tasks;
   PackHeader* h = reinterpret_cast<PackHeader*>(p->table_host);
-  int64_t* pre = reinterpret_cast<int64_t*>(p->table_host + sizeof(PackHeader));
-  int64_t* pre_prep = pre;
-  int64_t* pre_mul = pre + (m + 1);
-  int64_t* pre_cmp = pre + 2 * (m + 1);
-  PackTask* tt = reinterpret_cast<PackTask*>(pre + 3 * (m + 1));
+  PackTask* tt = reinterpret_cast<PackTask*>(p->table_host + sizeof(PackHeader));
   if (++p->seq == 0 || (uint32_t)p->seq == 0) p->seq += 1;
   h->ntasks = n;
   h->max_tasks = m;
@@ -2276,8 +2340,8 @@ kp_status kp_pack_run(kp_pack* p, int32_t* const* out_exps, void* const* out_coe
   h->pad = 0;
   h->seq = p->seq;
   h->post = p->post_dev + (size_t)m * 2 * 2 * KP_MAX_VARS;
-  pre_prep[0] = pre_mul[0] = pre_cmp[0] = 0;
-  char* base = static_cast<char*>(arena);
+  h->units = n > 0 ? reinterpret_cast<PackUnit*>(static_cast<char*>(arena) + p->units_off) : nullptr;
+  h->nunits = 0;
   for (int k = 0; k < n; ++k) {
     const kp_pack_task& t = p->tasks[(size_t)k];
     const size_t K = (size_t)k;
@@ -2288,44 +2352,18 @@ kp_status kp_pack_run(kp_pack* p, int32_t* const* out_exps, void* const* out_coe
     T.bx = t.b_exps;
     T.ac = t.a_coef;
     T.bc = t.b_coef;
-    T.na = t.na;
-    T.nb = t.nb;
-    char* q = base + p->off[K];
-    T.ak = reinterpret_cast<int64_t*>(q);
-    q += align_up(8 * (size_t)t.na);
-    T.bk = reinterpret_cast<int64_t*>(q);
-    q += align_up(8 * (size_t)t.nb);
-    T.table = reinterpret_cast<uint64_t*>(q);
-    T.slots = p->slots[K];
-    T.direct = p->direct[K];
-    const int64_t words = T.direct ? T.slots : 2 * T.slots;
-    q += align_up(8 * (size_t)std::max<int64_t>(words, 1));
-    T.count = reinterpret_cast<unsigned long long*>(q);
+    Carver c;
+    c.base = static_cast<char*>(arena);
+    c.off = (size_t)p->off[K];
+    (void)pack_task(c, t, p->layouts[K], p->caps[K], &T);
     T.f64 = t.dtype == KP_F64 ? 1 : 0;
     T.out_x = p->caps[K] > 0 ? out_exps[k] : nullptr;
     T.out_c = p->caps[K] > 0 ? out_coef[k] : nullptr;
     T.out_cap = p->caps[K];
-    // multiply units: rows of A by blocks of PACK_BLOCK terms of B, about
-    // 2^14 pairs each
-    const int64_t bw = std::min<int64_t>(std::max<int64_t>(t.nb, 1), PACK_BLOCK);
-    T.rows = std::max<int64_t>(1, std::min<int64_t>(std::max<int64_t>(t.na, 1), 16384 / bw));
-    T.bblocks = (t.nb + PACK_BLOCK - 1) / PACK_BLOCK;
-    const int64_t live = p->caps[K] > 0 ? 1 : 0;   // an empty product makes no pairs
-    const int64_t enc = (t.na + PACK_BLOCK - 1) / PACK_BLOCK + (t.nb + PACK_BLOCK - 1) / PACK_BLOCK;
-    const int64_t clr = std::max<int64_t>(1, (words + 4 * PACK_BLOCK - 1) / (4 * PACK_BLOCK));
-    const int64_t mul = live * ((t.na + T.rows - 1) / T.rows) * T.bblocks;
-    const int64_t cmp = (T.slots + 8 * PACK_BLOCK - 1) / (8 * PACK_BLOCK);
-    pre_prep[k + 1] = pre_prep[k] + live * enc + clr;
-    pre_mul[k + 1] = pre_mul[k] + mul;
-    pre_cmp[k + 1] = pre_cmp[k] + cmp;
-    if (!live) {   // nothing to encode: the prep units are the clearing ones
-      T.na = T.nb = 0;
-    }
   }
   int prev = 0;
   (void)hipGetDevice(&prev);
   (void)hipSetDevice(ctx->device);
-  const int grid = std::max(1, ctx->num_cu * 4);
   hipError_t e = hipSuccess;
   if (flags & KP_PACK_GRAPH) {
     if (!p->exec) {
@@ -2335,7 +2373,7 @@ kp_status kp_pack_run(kp_pack* p, int32_t* const* out_exps, void* const* out_coe
       if (e == hipSuccess) {
         hipError_t e1 = hipMemcpyAsync(p->table_dev, p->table_host, p->table_bytes,
                                        hipMemcpyHostToDevice, stream);
-        if (e1 == hipSuccess) e1 = launch_pack_run(p->table_dev, grid, stream);
+        if (e1 == hipSuccess) e1 = launch_pack_run(p->table_dev, m, ctx->num_cu, stream);
         hipGraph_t g = nullptr;
         e = hipStreamEndCapture(stream, &g);
         if (e1 != hipSuccess) e = e1;
@@ -2350,7 +2388,7 @@ kp_status kp_pack_run(kp_pack* p, int32_t* const* out_exps, void* const* out_coe
     if (e == hipSuccess) e = hipGraphLaunch(p->exec, stream);
   } else {
     e = hipMemcpyAsync(p->table_dev, p->table_host, p->table_bytes, hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess) e = launch_pack_run(p->table_dev, grid, stream);
+    if (e == hipSuccess) e = launch_pack_run(p->table_dev, m, ctx->num_cu, stream);
   }
   (void)hipSetDevice(prev);
   if (e != hipSuccess) return hip_fail(ctx, e, "kp_pack_run");

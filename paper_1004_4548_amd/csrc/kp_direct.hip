@@ -40,51 +40,6 @@ constexpr int STACK = 72;
 constexpr int ROWS = 1;     // rows per lane and batch
 constexpr int STEPS = 2;    // candidates per lane with their loads in flight
 
-// ------------------------------------------------------------ wave scans
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ uint32_t dpp0(uint32_t x) {   // lanes without a source read 0
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROW_MASK, 0xf, false);
-}
-// Inclusive sum and maximum over the lanes below (row shifts, then the row
-// broadcasts of lanes 15 and 31).
-__device__ __forceinline__ uint32_t wave_scan_add(uint32_t x) {
-  x += dpp0<0x111, 0xf>(x);
-  x += dpp0<0x112, 0xf>(x);
-  x += dpp0<0x114, 0xf>(x);
-  x += dpp0<0x118, 0xf>(x);
-  x += dpp0<0x142, 0xa>(x);
-  x += dpp0<0x143, 0xc>(x);
-  return x;
-}
-__device__ __forceinline__ uint32_t wave_scan_max(uint32_t x) {
-  x = max(x, dpp0<0x111, 0xf>(x));
-  x = max(x, dpp0<0x112, 0xf>(x));
-  x = max(x, dpp0<0x114, 0xf>(x));
-  x = max(x, dpp0<0x118, 0xf>(x));
-  x = max(x, dpp0<0x142, 0xa>(x));
-  x = max(x, dpp0<0x143, 0xc>(x));
-  return x;
-}
-__device__ __forceinline__ uint32_t lane_value(uint32_t x, int lane) {
-  return (uint32_t)__builtin_amdgcn_readlane((int)x, lane);
-}
-// a value that is the same in every lane, in scalar registers
-__device__ __forceinline__ uint32_t uniform(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
-}
-__device__ __forceinline__ uint64_t uniform(uint64_t x) {
-  return ((uint64_t)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x);
-}
-__device__ __forceinline__ int64_t uniform(int64_t x) {
-  return (int64_t)(((uint64_t)uniform((uint32_t)((uint64_t)x >> 32)) << 32) |
-                   uniform((uint32_t)(uint64_t)x));
-}
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // A bijection of 32 bits whose top bits depend on all of the key's: products'
 // codes are sums of digits times strides, which a multiplication alone leaves
 // clustered.

@@ -219,6 +219,84 @@ __device__ inline uint32_t wave_and(uint32_t v) {
   for (int off = 32; off > 0; off >>= 1) v &= (uint32_t)__shfl_xor((int)v, off);
   return v;
 }
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t dpp0(uint32_t x) {   // lanes without a source read 0
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROW_MASK, 0xf, false);
+}
+// Inclusive sum and maximum over the lanes below (row shifts, then the row
+// broadcasts of lanes 15 and 31).
+__device__ __forceinline__ uint32_t wave_scan_add(uint32_t x) {
+  x += dpp0<0x111, 0xf>(x);
+  x += dpp0<0x112, 0xf>(x);
+  x += dpp0<0x114, 0xf>(x);
+  x += dpp0<0x118, 0xf>(x);
+  x += dpp0<0x142, 0xa>(x);
+  x += dpp0<0x143, 0xc>(x);
+  return x;
+}
+__device__ __forceinline__ uint32_t wave_scan_max(uint32_t x) {
+  x = max(x, dpp0<0x111, 0xf>(x));
+  x = max(x, dpp0<0x112, 0xf>(x));
+  x = max(x, dpp0<0x114, 0xf>(x));
+  x = max(x, dpp0<0x118, 0xf>(x));
+  x = max(x, dpp0<0x142, 0xa>(x));
+  x = max(x, dpp0<0x143, 0xc>(x));
+  return x;
+}
+__device__ __forceinline__ uint32_t lane_value(uint32_t x, int lane) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, lane);
+}
+// a value that is the same in every lane, in scalar registers
+__device__ __forceinline__ uint32_t uniform(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+}
+__device__ __forceinline__ uint64_t uniform(uint64_t x) {
+  return ((uint64_t)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x);
+}
+__device__ __forceinline__ int64_t uniform(int64_t x) {
+  return (int64_t)(((uint64_t)uniform((uint32_t)((uint64_t)x >> 32)) << 32) |
+                   uniform((uint32_t)(uint64_t)x));
+}
+// First index of [j0, j1) whose sorted key is at least x (j1: none).
+__device__ __forceinline__ uint32_t first_from(const int64_t* k, uint32_t j0, uint32_t j1,
+                                               int64_t x) {
+  while (j0 < j1) {
+    const uint32_t m = (j0 + j1) >> 1;
+    if (k[m] < x) j0 = m + 1;
+    else j1 = m;
+  }
+  return j0;
+}
+// Sorts n keys in LDS (n a power of two); the workgroup's NT threads call it
+// together, before and after a barrier of theirs.
+template <int NT>
+__device__ __forceinline__ void block_sort(int64_t* key, int n) {
+  for (int size = 2; size <= n; size <<= 1)
+    for (int d = size >> 1; d > 0; d >>= 1) {
+      for (int t = threadIdx.x; t < n / 2; t += NT) {
+        const int i = 2 * t - (t & (d - 1)), j = i + d;   // bit d of i is clear
+        const int64_t x = key[i], y = key[j];
+        if ((x > y) == ((i & size) == 0)) {
+          key[i] = y;
+          key[j] = x;
+        }
+      }
+      __syncthreads();
+    }
+}
+// An index below n from a counter, evenly spread.
+__device__ __forceinline__ int64_t sample_of(uint32_t i, uint32_t seed, int64_t n) {
+  uint32_t h = (i + seed) * 0x9E3779B1u;
+  h = (h ^ (h >> 15)) * 0x85EBCA6Bu;
+  h = (h ^ (h >> 13)) * 0xC2B2AE35u;
+  h ^= h >> 16;
+  return (int64_t)(((uint64_t)h * (uint64_t)n) >> 32);   // n < 2^32
+}
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 #endif
 
 // ------------------------------------------------------------ workspace meta
@@ -244,6 +322,7 @@ struct Meta {
   uint32_t set_err[2];
   unsigned long long set_min[2], set_max[2];
   uint32_t zeros;
+  uint32_t crowd;                  // the columns are crowded (CROWDED)
 };
 
 // Status block owned by a context (device memory, 256 bytes).
@@ -576,6 +655,10 @@ constexpr int64_t DIRECT_ROWS = 24000;
 // against 0.27.
 constexpr int64_t DIRECT_SMALL_ROWS = 2048;
 constexpr int64_t DIRECT_PLACE = 4096;  // larger sets are placed by a launch of their own
+// Columns at most: crowded ones are sorted by counting within their bucket,
+// 3.5 ms for this many in one bucket.
+constexpr int64_t DIRECT_COLUMNS = 1 << 18;
+constexpr int DIRECT_CROWD_CELLS = 8192;   // sampled cells at most
 // A factor's terms by bucket of their code.
 struct DirectSet {
   const int64_t* k_in; const uint64_t* c_in;
@@ -594,8 +677,13 @@ struct DirectArgs {
   int64_t ncodes;                // codes of the product
   int32_t cw;
   int64_t ncell;                 // cells of 2^cw codes
-  int64_t* ccount;               // [ncell] products (bound)
+  int64_t* ccount;               // [ncell, at least ncrowd] products (bound)
   int64_t target, max_units;     // products per interval, intervals at most
+  int64_t grid;                  // intervals of a product whose columns are not crowded, at most
+  // for crowded columns: cells of sampled bounds, codes and terms by bucket
+  int32_t ncrowd;                // cells then, a power of two
+  int64_t* bounds;               // [ncrowd + 1]
+  int64_t* tmp_k; int32_t* tmp_i;   // [terms of the columns]
   int32_t small;                 // small intervals (DIRECT_SMALL_PRODUCTS)
   int32_t wide_codes;            // cells of more than 2^31 codes: 64-bit offsets
   longlong2* units;              // [max_units] {first code, codes}
@@ -616,41 +704,70 @@ hipError_t direct_setup();
 hipError_t launch_direct(const DirectArgs& R, kp_dtype dt, int64_t* out_n, uint32_t* ctx_err,
                          Mailbox* mb, uint64_t seq, hipStream_t s);
 
+// Columns are crowded when a term shares its bucket with more than this many
+// on average, or with this many times a bucket's even share.  Random sparse
+// terms share one with 2 to 3.5; 600 x 900 terms of five variables in [0, 30)
+// in a box that one outlier makes 50 times as wide share one with 50, and took
+// 2.8 ms instead of 0.27 while they were not treated as crowded.
+constexpr int CROWDED = 12;
+
 // packed batches (kp_pack.hip): many whole Laurent products in one fixed
 // sequence of persistent launches that read a device task table
 constexpr int PACK_BLOCK = 256;
+constexpr int PACK_CELLS = 256;        // cells of a task at most
+constexpr int PACK_CROWD_CELLS = 4096; // cells of a task with crowded columns at most
+constexpr int PACK_BUCKETS = 16384;    // buckets of a factor at most
+constexpr int PACK_HASHED = 1229;      // products of a hashed interval (60 % of its table)
+constexpr int PACK_DENSE = 4096;       // products of a directly indexed interval
+// A factor's terms by bucket of 2^shift codes (arena).
+struct PackSet {
+  int64_t n, maxc;
+  int32_t shift, nbk;
+  int32_t* rank; int32_t* start;       // [n], [nbk + 1]
+  int64_t* k; uint64_t* c;             // [n] codes, coefficients
+};
 struct PackTask {
   DevLayout la, lb;                 // A's and B's code maps; the product's decode
   const int32_t* ax;                // exponents [na][nx], [nb][nx]
   const int32_t* bx;
   const void* ac;                   // coefficients (int64 or double)
   const void* bc;
-  int64_t na, nb;
-  int64_t* ak;                      // codes (arena)
-  int64_t* bk;
-  uint64_t* table;                  // direct: one word per code; hash: (code + 1, value) pairs
-  int64_t slots;                    // direct: codes; hash: a power of two
-  int64_t rows;                     // rows of A per multiply unit
-  int64_t bblocks;                  // blocks of PACK_BLOCK terms of B
-  int32_t direct, f64;
+  PackSet set[2];                   // rows (the factor of fewer terms), columns
+  int64_t nkeys;                    // codes of the product
+  int32_t swap, f64;                // swap: the rows are B's terms
+  int32_t cw, ncell;                // cells of 2^cw codes
+  unsigned long long* cells;        // [cells of the task] products (arena)
+  int64_t max_units;                // intervals at most
+  // for crowded columns (arena): bounds of the cells, codes and terms by bucket
+  uint32_t* crowd;                  // whether they are
+  int32_t ncrowd;                   // cells then, a power of two
+  int64_t* bounds;                  // [ncrowd + 1]
+  int64_t* tmp_k; int32_t* tmp_i;   // [terms of the columns]
   int32_t* out_x;                   // [out_cap][nx]
   void* out_c;                      // [out_cap]
   int64_t out_cap;
   unsigned long long* count;        // arena
 };
-// The table: this header, then three unit prefixes of max_tasks + 1 words
-// (prep, multiply, compaction), then max_tasks tasks.
+// An interval of output codes of one task.
+struct PackUnit {
+  int64_t lo, width;
+  int64_t task;
+};
+// The table: this header, then max_tasks tasks.
 struct PackHeader {
   int32_t ntasks, max_tasks;
   uint32_t err;
   uint32_t pad;
   uint64_t seq;                     // tag of this run's posts
   uint64_t* post;                   // host-mapped: two tagged words per task
+  PackUnit* units;                  // intervals of every task (arena)
+  unsigned long long nunits;        // how many
 };
 size_t pack_table_bytes(int max_tasks);
 hipError_t launch_pack_boxes(const int32_t* const* vals, const int64_t* n, const int32_t* nv,
                              int nseg, uint64_t* post_dev, uint64_t seq, hipStream_t s);
-hipError_t launch_pack_run(void* table_dev, int grid, hipStream_t s);
+hipError_t pack_setup();
+hipError_t launch_pack_run(void* table_dev, int max_tasks, int num_cu, hipStream_t s);
 
 // diagnostics (kp_diag.hip)
 hipError_t probe_lds_atomic(int pattern, int blocks, int iters, unsigned long long* sink,

@@ -2,21 +2,28 @@
 // persistent launches.
 //
 // A pack keeps the products of a batch in a device task table.  Each stage is
-// one launch of a fixed grid whose workgroups walk the units of every task
-// (a unit is a slice of one task's work: terms to encode, table words to
-// clear, a block of term pairs, a block of table slots); unit u belongs to the
-// task whose prefix of units covers it.  The kernels read nothing but the
-// table, so the sequence (the table's upload included) can be captured once
-// into a HIP graph and replayed for every batch, whatever its products.
+// one launch of a fixed grid whose workgroups walk the work of every task, and
+// the kernels read nothing but the table, so the sequence (the table's upload
+// included) can be captured once into a HIP graph and replayed for every
+// batch, whatever its products.
 //
 // Each product is the schoolbook sum of Section 3 over Kronecker codes
-// (Section 2), accumulated in a table of its own in device memory: indexed by
-// code when the key space is small (the dense array of Section 3.1), else an
-// open-addressing hash table keyed by code, with a compare-and-swap on the key
-// and an atomic add on the coefficient (Section 3.2).  Nonzero sums are
-// compacted by wavefront ballots and decoded to exponents on the way out, and
-// each task's count is posted to pinned host memory.
+// (Section 2), restricted to intervals of output codes as Section 4 restricts
+// threads: a workgroup finds the products of an interval from the factors
+// sorted by code and adds them in LDS, indexed by code when the interval is no
+// wider than the table (the dense array of Section 3.1), else in an
+// open-addressing hash table keyed by code (Section 3.2).  Nonzero sums are
+// decoded to exponents on the way out, and each task's count is posted to
+// pinned host memory.
+//
+// The products used to be added in tables in device memory, one atomic or two
+// per product: 1.07e7 products of 24 tasks of 50 to 2,000 terms took 1.31 ms,
+// bound by atomics on the same few lines (8e9 a second), and 0.29 ms more to
+// read the tables back (2.00 ms the whole batch).  In LDS they take 0.40 ms and
+// nothing is read back; with sorting, counting and planning 0.46 ms (0.71 the
+// batch).
 
+#include <algorithm>
 #include <climits>
 
 #include "kp_internal.h"
@@ -26,39 +33,21 @@ namespace kp {
 namespace {
 
 constexpr int PACK_BOX_BLOCK = 1024;
-constexpr int PACK_SLOTS_PER_THREAD = 8;
-constexpr int PACK_CMP_SLOTS = PACK_BLOCK * PACK_SLOTS_PER_THREAD;
-constexpr uint64_t GOLD = 0x9E3779B97F4A7C15ull;   // 2^64 / golden ratio (Fibonacci hashing)
+constexpr int PACK_SORT_BLOCK = 1024;
+constexpr int PACK_SLOTS = 2048;        // of an interval's table in LDS
+constexpr int PACK_STEPS = 2;           // candidates per lane with their loads in flight
+constexpr int PACK_MAX_PROBE = 48;      // longer chains: the table counts as full
+constexpr int PACK_PER_CU = 3;          // multiplying workgroups that fit a compute unit (LDS)
+constexpr int PACK_STACK = 104;         // intervals still to do (three more per cut)
 
 struct PackView {
   PackHeader* h;
-  const int64_t* pre_prep;
-  const int64_t* pre_mul;
-  const int64_t* pre_cmp;
   PackTask* tasks;
 };
 
 __device__ __forceinline__ PackView view(void* table) {
-  PackView v;
-  v.h = static_cast<PackHeader*>(table);
-  const int m = v.h->max_tasks;
-  int64_t* pre = reinterpret_cast<int64_t*>(static_cast<char*>(table) + sizeof(PackHeader));
-  v.pre_prep = pre;
-  v.pre_mul = pre + (m + 1);
-  v.pre_cmp = pre + 2 * (m + 1);
-  v.tasks = reinterpret_cast<PackTask*>(pre + 3 * (m + 1));
-  return v;
-}
-
-// The task of unit u: the last k with pre[k] <= u (pre ascending, pre[0] = 0).
-__device__ __forceinline__ int task_of(const int64_t* pre, int n, int64_t u) {
-  int a = 0, z = n;
-  while (z - a > 1) {
-    const int m = (a + z) >> 1;
-    if (pre[m] <= u) a = m;
-    else z = m;
-  }
-  return a;
+  return PackView{static_cast<PackHeader*>(table),
+                  reinterpret_cast<PackTask*>(static_cast<char*>(table) + sizeof(PackHeader))};
 }
 
 // ------------------------------------------------------------ boxes
@@ -119,190 +108,506 @@ k_pack_boxes(const int32_t* const* vals, const int64_t* ns, const int32_t* nvs, 
   }
 }
 
-// ------------------------------------------------------------ prep
-// Units of a task: its rows of A and of B to encode (PACK_BLOCK each), then
-// its table words to clear (4 * PACK_BLOCK each, at least one unit); the first
-// clearing unit also resets the task's result counter.
-__global__ void __launch_bounds__(PACK_BLOCK) k_pack_prep(void* table) {
+// ------------------------------------------------------------ sort
+// One workgroup per (task, factor): codes of the terms, bucket histogram in
+// LDS, bucket starts, and the terms by bucket (encoded twice rather than kept:
+// a factor of a pack has some hundreds of terms).  Crowded columns are sorted
+// within their buckets too, so that an interval finds exactly its own, and the
+// task's cells are then bounded by a sorted sample of its products instead of
+// being equally wide: a product of two factors of 600 terms crowded in one of
+// 16,384 buckets would otherwise be one workgroup's work, with every product
+// looked at for every interval.
+__global__ void __launch_bounds__(PACK_SORT_BLOCK) k_pack_sort(void* table) {
+  extern __shared__ __align__(8) int32_t hist[];
+  __shared__ uint32_t s_ws[PACK_SORT_BLOCK / 64];
+  __shared__ unsigned long long s_sq;
   const PackView P = view(table);
-  const int nt = P.h->ntasks;
-  const int64_t total = P.pre_prep[nt];
-  for (int64_t u = blockIdx.x; u < total; u += gridDim.x) {
-    const int k = task_of(P.pre_prep, nt, u);
-    const PackTask& T = P.tasks[k];
-    int64_t l = u - P.pre_prep[k];
-    const int64_t ea = (T.na + PACK_BLOCK - 1) / PACK_BLOCK;
-    const int64_t eb = (T.nb + PACK_BLOCK - 1) / PACK_BLOCK;
-    if (l < ea + eb) {
-      const bool isb = l >= ea;
-      const int64_t r = (isb ? l - ea : l) * PACK_BLOCK + threadIdx.x;
-      const int64_t n = isb ? T.nb : T.na;
-      if (r < n) {
-        const DevLayout& L = isb ? T.lb : T.la;
-        const int32_t* x = (isb ? T.bx : T.ax) + r * L.nx;
-        int32_t e[KP_MAX_VARS];
-        for (int v = 0; v < L.nx; ++v) e[v] = x[v];
-        int64_t kx = 0, ky = 0;
-        const uint32_t bad = encode_term(L, e, nullptr, 0, &kx, &ky);
-        if (bad) atomicOr(&P.h->err, bad);
-        (isb ? T.bk : T.ak)[r] = kx;
-      }
-    } else {
-      l -= ea + eb;
-      const int64_t words = T.direct ? T.slots : 2 * T.slots;
-      const int64_t w0 = l * 4 * PACK_BLOCK + threadIdx.x;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int64_t w = w0 + (int64_t)q * PACK_BLOCK;
-        if (w < words) T.table[w] = 0;
-      }
-      if (l == 0 && threadIdx.x == 0) *T.count = 0;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int u = blockIdx.x; u < 2 * P.h->ntasks; u += gridDim.x) {
+    const PackTask& T = P.tasks[u >> 1];
+    const int role = u & 1;                       // 0: rows, 1: columns
+    const bool isb = (role == 1) != (T.swap != 0);
+    const PackSet& S = T.set[role];
+    const uint64_t* __restrict__ c = static_cast<const uint64_t*>(isb ? T.bc : T.ac);
+    if (role == 0) {
+      if (tid == 0) *T.count = 0;
+      for (int k = tid; k < T.ncrowd && S.n > 0; k += PACK_SORT_BLOCK) T.cells[k] = 0;
     }
+    if (tid == 0) s_sq = 0;
+    for (int k = tid; k < S.nbk; k += PACK_SORT_BLOCK) hist[k] = 0;
+    __syncthreads();
+    uint32_t bad = 0;
+    // (codes outside the planned box are reported; the clamp keeps them inside
+    // the buckets)
+    const auto code_in = [&](const DevLayout& L, const int32_t* __restrict__ x, int64_t maxc,
+                             int64_t r) -> int64_t {
+      int64_t k = 0;
+      for (int v = 0; v < L.nx; ++v) {
+        const int32_t e = x[r * L.nx + v];
+        if (e < L.fmin[v] || e > L.fmax[v]) bad |= ERR_RANGE;
+        k += L.xc[v] * (int64_t)(e - L.fmin[v]);
+      }
+      return k < 0 ? 0 : k > maxc ? maxc : k;
+    };
+    const auto code_of = [&](int64_t r) {
+      return code_in(isb ? T.lb : T.la, isb ? T.bx : T.ax, S.maxc, r);
+    };
+    for (int64_t r = tid; r < S.n; r += PACK_SORT_BLOCK)
+      S.rank[r] = atomicAdd(&hist[code_of(r) >> S.shift], 1);
+    __syncthreads();
+    // exclusive scan: each wavefront a contiguous stretch of buckets, 64 at a time
+    const int per = (S.nbk + PACK_SORT_BLOCK - 1) / PACK_SORT_BLOCK * 64;
+    const int b0 = min(S.nbk, wave * per), b1 = min(S.nbk, b0 + per);
+    uint32_t sum = 0;
+    uint64_t sq = 0;
+    for (int b = b0; b < b1; b += 64) {
+      const uint32_t v = b + lane < b1 ? (uint32_t)hist[b + lane] : 0u;
+      sum += lane_value(wave_scan_add(v), 63);
+      sq += (uint64_t)v * v;
+    }
+    if (lane == 0) s_ws[wave] = sum;
+    if (role == 1 && sq) atomicAdd(&s_sq, (unsigned long long)sq);
+    __syncthreads();
+    uint32_t run = 0;
+    for (int w = 0; w < wave; ++w) run += s_ws[w];
+    for (int b = b0; b < b1; b += 64) {
+      const uint32_t v = b + lane < b1 ? (uint32_t)hist[b + lane] : 0u;
+      const uint32_t incl = wave_scan_add(v);
+      if (b + lane < b1) hist[b + lane] = S.start[b + lane] = (int32_t)(run + incl - v);
+      run += lane_value(incl, 63);
+    }
+    if (tid == 0) S.start[S.nbk] = (int32_t)S.n;
+    __syncthreads();
+    // (a product of fewer than 64 codes a pair has directly indexed
+    // intervals, or not many times more: simplices share a bucket with 30, and
+    // exact intervals cost them 130 us of a batch's 710 for nothing)
+    const bool crowd = role == 1 && T.nkeys / 64 >= S.n * T.set[0].n &&
+                       s_sq > (uint64_t)CROWDED * (uint64_t)max(S.n, S.n * S.n / S.nbk);
+    if (role == 1 && tid == 0) *T.crowd = crowd ? 1u : 0u;
+    for (int64_t r = tid; r < S.n; r += PACK_SORT_BLOCK) {
+      const int64_t k = code_of(r);
+      const int64_t at = hist[k >> S.shift] + S.rank[r];
+      if (crowd) {
+        T.tmp_k[at] = k;
+        T.tmp_i[at] = (int32_t)r;
+      } else {
+        S.k[at] = k;
+        S.c[at] = c[r];
+      }
+    }
+    if (crowd) {   // the same for every thread
+      __syncthreads();
+      for (int64_t t = tid; t < S.n; t += PACK_SORT_BLOCK) {
+        const int64_t k = T.tmp_k[t], b = k >> S.shift;
+        const int e = b + 1 < S.nbk ? hist[b + 1] : (int)S.n;
+        int at = hist[b];
+#pragma unroll 4
+        for (int o = hist[b]; o < e; ++o) {
+          const int64_t y = T.tmp_k[o];
+          at += y < k || (y == k && o < t) ? 1 : 0;
+        }
+        S.k[at] = k;
+        S.c[at] = c[T.tmp_i[t]];
+      }
+      __syncthreads();   // hist has been read
+      const PackSet& A = T.set[0];
+      int64_t* key = reinterpret_cast<int64_t*>(hist);
+      for (int o = tid; o < T.ncrowd; o += PACK_SORT_BLOCK)
+        key[o] = code_in(isb ? T.la : T.lb, isb ? T.ax : T.bx, A.maxc, sample_of(o, 0, A.n)) +
+                 code_of(sample_of(o, PACK_CROWD_CELLS, S.n));
+      __syncthreads();
+      block_sort<PACK_SORT_BLOCK>(key, T.ncrowd);
+      for (int o = tid; o <= T.ncrowd; o += PACK_SORT_BLOCK)
+        T.bounds[o] = o == 0 ? 0 : o == T.ncrowd ? T.nkeys : key[o];
+    }
+    if (bad) atomicOr(&P.h->err, bad);
+    __syncthreads();   // the next factor clears hist
+  }
+}
+
+// ------------------------------------------------------------ intervals
+// Cell c of a task: its first code and the one after its last (no cell: both 0).
+__device__ __forceinline__ void cell_of(const PackTask& T, bool crowd, int c, int64_t* lo,
+                                        int64_t* end) {
+  *lo = *end = 0;
+  if (crowd) {
+    *lo = T.bounds[c];
+    *end = T.bounds[c + 1];
+  } else if (c < T.ncell) {
+    *lo = (int64_t)c << T.cw;
+    *end = min(T.nkeys, *lo + ((int64_t)1 << T.cw));
+  }
+}
+// The columns of codes xlo .. xhi (in a crowded task exactly, else their
+// whole buckets).
+__device__ __forceinline__ void columns_of(const PackSet& B, bool crowd, int64_t xlo, int64_t xhi,
+                                           uint32_t* j0, uint32_t* j1) {
+  const int64_t lo = max((int64_t)0, min(xlo, B.maxc)), hi = max((int64_t)0, min(xhi, B.maxc));
+  const int64_t q0 = lo >> B.shift, q1 = hi >> B.shift;
+  *j0 = (uint32_t)B.start[q0];
+  *j1 = (uint32_t)B.start[q1 + 1];
+  if (crowd) {   // (each end by itself: they may lie in one bucket or in two)
+    *j0 = first_from(B.k, *j0, (uint32_t)B.start[q0 + 1], lo);
+    *j1 = first_from(B.k, (uint32_t)B.start[q1], *j1, hi + 1);
+  }
+}
+
+// The products of each cell of 2^cw codes (whole buckets of the columns: a
+// bound): one workgroup per task, 64 cells and a quarter of the rows, a cell
+// per lane and a slice of the rows per wavefront, four rows' loads in flight.
+__global__ void __launch_bounds__(PACK_BLOCK) k_pack_count(void* table) {
+  constexpr int GROUPS = PACK_CELLS / 64, QUARTERS = 4;
+  __shared__ unsigned long long s_count[64];
+  const PackView P = view(table);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int units = P.h->ntasks * GROUPS * QUARTERS;
+  for (int u = blockIdx.x; u < units; u += gridDim.x) {
+    const PackTask& T = P.tasks[u / (GROUPS * QUARTERS)];
+    const int group = (u / QUARTERS) % GROUPS, quarter = u % QUARTERS;
+    const int64_t* __restrict__ ak = T.set[0].k;
+    const PackSet B = T.set[1];
+    const int64_t an = T.set[0].n, per = (an + QUARTERS - 1) / QUARTERS;
+    const bool crowd = B.n > 0 && *T.crowd != 0;
+    const int64_t i1 = min(an, per * (quarter + 1));
+    for (int c0 = group * 64; c0 < (crowd ? T.ncrowd : T.ncell); c0 += GROUPS * 64) {
+      const int c = c0 + lane;
+      if (tid < 64) s_count[tid] = 0;
+      __syncthreads();
+      int64_t lo, hi;
+      cell_of(T, crowd, c, &lo, &hi);
+      if (hi > lo) {
+        hi -= 1;
+        unsigned long long n = 0;
+#pragma unroll 4
+        for (int64_t i = per * quarter + wave; i < i1; i += PACK_BLOCK / 64) {
+          const int64_t a = ak[i], xlo = lo - a, xhi = hi - a;
+          uint32_t j0, j1;
+          columns_of(B, crowd, xlo, xhi, &j0, &j1);
+          n += xhi >= 0 && xlo <= B.maxc ? (unsigned long long)(j1 - j0) : 0ull;
+        }
+        if (n) atomicAdd(&s_count[lane], n);
+      }
+      __syncthreads();
+      if (tid < 64 && s_count[lane]) atomicAdd(&T.cells[c], s_count[lane]);
+      __syncthreads();   // the next cells clear s_count
+    }
+  }
+}
+
+// One workgroup per task: the intervals of its cells.  A cell is cut into
+// intervals that the table indexes directly (at most PACK_SLOTS codes, about
+// PACK_DENSE products) or into hashed ones of about PACK_HASHED products,
+// whichever are fewer.
+__global__ void __launch_bounds__(PACK_BLOCK) k_pack_plan(void* table) {
+  __shared__ int64_t s_ws[PACK_BLOCK / 64];
+  __shared__ int64_t s_first;
+  const PackView P = view(table);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int t = blockIdx.x; t < P.h->ntasks; t += gridDim.x) {
+    const PackTask& T = P.tasks[t];
+    const bool live = T.set[1].n > 0, crowd = live && *T.crowd != 0;
+    const int cells = live ? (crowd ? T.ncrowd : T.ncell) : 0;
+    const int per = (cells + PACK_BLOCK - 1) / PACK_BLOCK;
+    const int c0 = min(cells, tid * per), c1 = min(cells, c0 + per);
+    const auto block_sum = [&](int64_t v, int64_t* before) -> int64_t {
+      int64_t incl = v;
+      for (int off = 1; off < 64; off <<= 1) {
+        const int64_t y = __shfl_up(incl, off);
+        if (lane >= off) incl += y;
+      }
+      __syncthreads();
+      if (lane == 63) s_ws[wave] = incl;
+      __syncthreads();
+      int64_t tot = 0, b = 0;
+      for (int w = 0; w < PACK_BLOCK / 64; ++w) {
+        if (w < wave) b += s_ws[w];
+        tot += s_ws[w];
+      }
+      *before = b + incl - v;
+      return tot;
+    };
+    int64_t before, n = 0;
+    for (int c = c0; c < c1; ++c) n += (int64_t)T.cells[c];
+    const int64_t all = block_sum(n, &before);
+    // hashed intervals are made larger when they would outgrow the task's array
+    const int64_t room = max((int64_t)1, T.max_units - cells);
+    const int64_t target = max((int64_t)PACK_HASHED, (all + room - 1) / room);
+    const auto units_of = [&](int c, int64_t* lo, int64_t* width) -> int64_t {
+      const int64_t m = (int64_t)T.cells[c];
+      int64_t end;
+      cell_of(T, crowd, c, lo, &end);
+      *width = end - *lo;
+      if (m <= 0 || *width <= 0) return 0;
+      const int64_t hashed = (m + target - 1) / target;
+      const int64_t dense = max((m + PACK_DENSE - 1) / PACK_DENSE,
+                                (*width + PACK_SLOTS - 1) / PACK_SLOTS);
+      return min(min(hashed, dense), *width);
+    };
+    int64_t lo, width, mine = 0;
+    for (int c = c0; c < c1; ++c) mine += units_of(c, &lo, &width);
+    const int64_t total = block_sum(mine, &before);
+    if (tid == 0) s_first = (int64_t)atomicAdd(&P.h->nunits, (unsigned long long)total);
+    __syncthreads();
+    PackUnit* out = P.h->units + s_first + before;
+    for (int c = c0; c < c1; ++c) {
+      const int64_t k = units_of(c, &lo, &width);
+      const int64_t step = k ? (width + k - 1) / k : 0;
+      for (int64_t u = 0; u < k; ++u) {
+        const int64_t a = min(width, u * step), z = min(width, a + step);
+        *out++ = PackUnit{lo + a, z - a, t};
+      }
+    }
+    __syncthreads();   // the next task uses s_ws
   }
 }
 
 // ------------------------------------------------------------ multiply
-__device__ __forceinline__ void add_value(uint64_t* p, bool f64, uint64_t bits) {
+__device__ __forceinline__ void add_value(uint64_t* p, bool f64, uint64_t a, uint64_t b) {
   if (f64) {
-    double v;
-    __builtin_memcpy(&v, &bits, 8);
-    atomicAdd(reinterpret_cast<double*>(p), v);
+    atomicAdd(reinterpret_cast<double*>(p), __longlong_as_double((long long)a) *
+                                                __longlong_as_double((long long)b));
   } else {
-    atomicAdd(reinterpret_cast<unsigned long long*>(p), (unsigned long long)bits);
+    atomicAdd(reinterpret_cast<unsigned long long*>(p), (unsigned long long)(a * b));   // wraps modulo 2^64
   }
 }
 
-// Units of a task: (block of `rows` rows of A, block of PACK_BLOCK terms of B);
-// a thread takes one term of B against the block's rows (wavefront-uniform
-// loads of A).  Each product is added at its code: directly, or in the hash
-// table (linear probing from the code's Fibonacci hash).
-__global__ void __launch_bounds__(PACK_BLOCK) k_pack_mul(void* table) {
+__device__ __forceinline__ uint32_t pack_hash(uint64_t k) {   // top bits depend on all of k
+  uint32_t h = ((uint32_t)(k >> 32) * 0x9E3779B1u) ^ (uint32_t)k;
+  h *= 0x9E3779B1u;
+  h ^= h >> 15;
+  return h * 0x85EBCA6Bu;
+}
+
+// What the decode of one variable takes, and its exponent of the code whose
+// quotient by the widths before it is q.
+struct PackDigit {
+  FastDiv d;
+  FastDiv32 d32;
+  int32_t least;
+};
+__device__ __forceinline__ int32_t pack_digit(const PackDigit& D, uint64_t& q) {
+  uint32_t e;
+  if ((q >> 32) == 0 && D.d32.d != 0) {
+    const uint32_t n = (uint32_t)q, qq = fdiv32(n, D.d32);
+    e = n - qq * D.d32.d;
+    q = qq;
+  } else {
+    const uint64_t qq = fdiv(q, D.d);
+    e = (uint32_t)(q - qq * D.d.d);
+    q = qq;
+  }
+  return (int32_t)e + D.least;
+}
+
+// A set of the table in scalar registers.
+template <typename P>
+__device__ __forceinline__ P* uniform_ptr(P* p) {
+  return reinterpret_cast<P*>(uniform(reinterpret_cast<uint64_t>(p)));
+}
+__device__ __forceinline__ PackSet uniform_set(const PackSet& s) {
+  PackSet r;
+  r.n = uniform(s.n);
+  r.maxc = uniform(s.maxc);
+  r.shift = (int32_t)uniform((uint32_t)s.shift);
+  r.nbk = 0;
+  r.rank = nullptr;
+  r.start = uniform_ptr(s.start);
+  r.k = uniform_ptr(s.k);
+  r.c = uniform_ptr(s.c);
+  return r;
+}
+
+// What bounds it: the latency of row -> columns -> slot and VALU issue (three
+// workgroups of 50 KB of LDS per compute unit), not bytes.  Intervals are taken
+// at a fixed stride: handing them out from one counter cost 1.03 ms instead of
+// 0.41 on the batch named above, 64 coarser cells a task 1.2 ms, probe chains
+// of up to 256 slots 1.9 ms.
+// The grid takes the intervals of every task; see the head of the file.  A
+// full table (only codes crowded in part of a cell make one, intervals being
+// sized from their cell's products) has its interval cut in four; one of at
+// most PACK_SLOTS codes is indexed directly and always fits.
+__global__ void __launch_bounds__(PACK_BLOCK, PACK_PER_CU) k_pack_mul(void* table) {
+  constexpr int NW = PACK_BLOCK / 64, PER = PACK_SLOTS / PACK_BLOCK;
+  __shared__ uint64_t keys[PACK_SLOTS], vals[PACK_SLOTS];
+  __shared__ uint64_t row_off[NW][64], row_coef[NW][64];
+  __shared__ uint32_t row_col[NW][64];
+  __shared__ uint16_t seg[NW][PACK_STEPS * 64];
+  __shared__ uint32_t s_cnt[NW], s_next, s_over;
+  __shared__ int64_t s_base, s_lo[PACK_STACK];
+  __shared__ PackDigit s_dig[KP_MAX_VARS];   // the task's decode
+  __shared__ uint64_t s_width[PACK_STACK];
   const PackView P = view(table);
-  const int nt = P.h->ntasks;
-  const int64_t total = P.pre_mul[nt];
-  for (int64_t u = blockIdx.x; u < total; u += gridDim.x) {
-    const int k = task_of(P.pre_mul, nt, u);
-    const PackTask& T = P.tasks[k];
-    const int64_t l = u - P.pre_mul[k];
-    const int64_t rb = l / T.bblocks, bb = l - rb * T.bblocks;
-    const int64_t j = bb * PACK_BLOCK + threadIdx.x;
-    if (j >= T.nb) continue;
-    const int64_t kb = T.bk[j];
-    const uint64_t cb = static_cast<const uint64_t*>(T.bc)[j];
-    const int64_t i0 = rb * T.rows, i1 = min(T.na, i0 + T.rows);
-    const bool f64 = T.f64 != 0;
-    const uint64_t* ac = static_cast<const uint64_t*>(T.ac);
-    const uint64_t mask = (uint64_t)T.slots - 1;
-    const int shift = T.direct ? 0 : 64 - __builtin_ctzll((unsigned long long)T.slots);
-    for (int64_t i = i0; i < i1; ++i) {
-      const int64_t c = T.ak[i] + kb;
-      uint64_t bits;
-      if (f64) {
-        double x, y;
-        const uint64_t xa = ac[i];
-        __builtin_memcpy(&x, &xa, 8);
-        __builtin_memcpy(&y, &cb, 8);
-        const double v = x * y;
-        __builtin_memcpy(&bits, &v, 8);
-      } else {
-        bits = ac[i] * cb;   // wraps modulo 2^64
+  const unsigned long long units = P.h->nunits;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (unsigned long long u = blockIdx.x; u < units; u += gridDim.x) {
+    const PackUnit unit = P.h->units[u];
+    const PackTask& T = P.tasks[uniform((uint32_t)unit.task)];
+    const PackSet A = uniform_set(T.set[0]), B = uniform_set(T.set[1]);
+    const bool f64 = T.f64 != 0, crowd = *T.crowd != 0;
+    // (counts of a batch are 32-bit)
+    const uint32_t batch = B.n < ((int64_t)1 << 26) ? 64u : 1u;
+    const int nx = (int)uniform((uint32_t)T.la.nx);
+    if (tid < nx) s_dig[tid] = PackDigit{T.la.dx[tid], T.la.dx32[tid], (int32_t)T.la.xmin[tid]};
+    if (tid == 0) {
+      s_lo[0] = unit.lo;
+      s_width[0] = (uint64_t)unit.width;
+    }
+    __syncthreads();
+    for (int sp = 1; sp > 0;) {
+      --sp;
+      const int64_t lo = uniform(s_lo[sp]);
+      const uint64_t width = uniform(s_width[sp]);
+      const bool direct = width <= PACK_SLOTS;
+#pragma unroll
+      for (int r = 0; r < PER; ++r) {
+        keys[r * PACK_BLOCK + tid] = ~0ull;
+        vals[r * PACK_BLOCK + tid] = 0;
       }
-      if (T.direct) {
-        // codes lie in [0, slots) when the factors lie in their planned boxes
-        if ((uint64_t)c < (uint64_t)T.slots) add_value(T.table + c, f64, bits);
-        else atomicOr(&P.h->err, ERR_RANGE);
+      if (tid == 0) s_next = s_over = 0;
+      __syncthreads();
+      const int64_t hi = lo + (int64_t)width - 1, amin = lo - B.maxc;
+      uint32_t i0 = 0, i1 = 0;
+      if (width > 0 && amin <= A.maxc) {   // rows that meet the interval
+        i0 = (uint32_t)A.start[max((int64_t)0, amin) >> A.shift];
+        i1 = (uint32_t)A.start[(min(hi, A.maxc) >> A.shift) + 1];
+      }
+      for (;;) {
+        uint32_t bt = 0;
+        if (lane == 0) bt = atomicAdd(&s_next, batch);
+        const uint32_t ib = i0 + lane_value(bt, 0);
+        if (ib >= i1 || *(volatile uint32_t*)&s_over) break;
+        const uint32_t i = min(ib + lane, i1 - 1);
+        const int64_t a = A.k[i], xlo = lo - a, xhi = hi - a;
+        const bool in = lane < (int)batch && ib + lane < i1 && xhi >= 0 && xlo <= B.maxc;
+        uint32_t j0, j1;
+        columns_of(B, crowd, xlo, xhi, &j0, &j1);
+        const uint32_t cnt = in ? j1 - j0 : 0u;
+        const uint32_t incl = wave_scan_add(cnt), excl = incl - cnt;
+        const uint32_t total = lane_value(incl, 63);
+        wave_sync();
+        row_col[wave][lane] = j0 - excl;
+        row_off[wave][lane] = (uint64_t)(a - lo);
+        row_coef[wave][lane] = A.c[i];
+        uint32_t carry = 0;
+        // candidates 64 at a time: candidate q belongs to the last row whose
+        // first candidate is at or before it
+        for (uint32_t q0 = 0; q0 < total; q0 += PACK_STEPS * 64) {
+#pragma unroll
+          for (int v = 0; v < PACK_STEPS; ++v) seg[wave][v * 64 + lane] = 0;
+          wave_sync();
+          if (cnt && excl - q0 < PACK_STEPS * 64u) seg[wave][excl - q0] = (uint16_t)lane;
+          wave_sync();
+          uint64_t off[PACK_STEPS], ca[PACK_STEPS], cb[PACK_STEPS];
+#pragma unroll
+          for (int v = 0; v < PACK_STEPS; ++v) {
+            const uint32_t m = max(carry, wave_scan_max(seg[wave][v * 64 + lane]));
+            carry = lane_value(m, 63);
+            const uint32_t j = row_col[wave][m] + min(q0 + v * 64 + lane, total - 1);
+            off[v] = row_off[wave][m] + (uint64_t)B.k[j];
+            ca[v] = row_coef[wave][m];
+            cb[v] = B.c[j];
+          }
+          wave_sync();
+#pragma unroll
+          for (int v = 0; v < PACK_STEPS; ++v) {
+            if (q0 + v * 64 + lane >= total || off[v] >= width) continue;
+            uint32_t s = (uint32_t)off[v];
+            if (!direct) {
+              const unsigned long long key = off[v];
+              s = pack_hash(key) >> 21;
+              unsigned long long c =
+                  atomicCAS(reinterpret_cast<unsigned long long*>(&keys[s]), ~0ull, key);
+              int q = 0;
+#pragma nounroll
+              while (c != ~0ull && c != key && q < PACK_MAX_PROBE) {
+                ++q;
+                s = (s + 1) & (PACK_SLOTS - 1);
+                c = atomicCAS(reinterpret_cast<unsigned long long*>(&keys[s]), ~0ull, key);
+              }
+              if (c != ~0ull && c != key) {
+                s_over = 1;
+                continue;
+              }
+            }
+            add_value(&vals[s], f64, ca[v], cb[v]);
+          }
+        }
+      }
+      __syncthreads();
+      if (s_over) {   // the same for every thread
+        __syncthreads();
+        if (wave == 0) {
+          // cut at the quartiles of 64 of the table's keys
+          const uint64_t key = keys[lane * (PACK_SLOTS / 64)];
+          int rank = 0;
+#pragma unroll 8
+          for (int o = 0; o < 64; ++o) {
+            const uint64_t y = keys[o * (PACK_SLOTS / 64)];
+            rank += y < key || (y == key && o < lane) ? 1 : 0;
+          }
+          const int n = (int)__popcll(__ballot(key != ~0ull));
+          const bool few = n < 8;   // (then equally wide)
+          const uint64_t step = width / 4;
+          if (lane == 0) s_lo[sp] = lo;
+          if (few ? lane > 0 && lane < 4 : key != ~0ull && rank > 0 && rank % (n / 4) == 0 && rank / (n / 4) < 4) {
+            const int piece = few ? lane : rank / (n / 4);
+            s_lo[sp + piece] = lo + (int64_t)(few ? step * lane : key);
+          }
+        }
+        __syncthreads();
+        if (tid < 4)
+          s_width[sp + tid] = (uint64_t)((tid < 3 ? s_lo[sp + tid + 1] : hi + 1) - s_lo[sp + tid]);
+        sp += 4;
+        __syncthreads();
         continue;
       }
-      const unsigned long long key = (unsigned long long)c + 1;
-      uint64_t s = ((uint64_t)c * GOLD) >> shift;
-      int64_t q = 0;
-      for (; q < T.slots; ++q) {   // the table holds at least twice the task's terms
-        unsigned long long* ks = reinterpret_cast<unsigned long long*>(T.table + 2 * s);
-        unsigned long long cur = __hip_atomic_load(ks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (cur == 0) {
-          cur = atomicCAS(ks, 0ull, key);
-          if (cur == 0) cur = key;
-        }
-        if (cur == key) {
-          add_value(T.table + 2 * s + 1, f64, bits);
-          break;
-        }
-        s = (s + 1) & mask;
-      }
-      if (q == T.slots) atomicOr(&P.h->err, ERR_CAPACITY);
-    }
-  }
-}
-
-// ------------------------------------------------------------ compaction
-// Units of a task: blocks of PACK_CMP_SLOTS table slots.  Nonzero sums are
-// compacted by ballots, placed after one atomic on the task's counter, and
-// written as decoded exponents and coefficients.
-__global__ void __launch_bounds__(PACK_BLOCK) k_pack_compact(void* table) {
-  __shared__ int64_t s_wave[PACK_BLOCK / 64];
-  __shared__ int64_t s_base;
-  const PackView P = view(table);
-  const int nt = P.h->ntasks;
-  const int64_t total = P.pre_cmp[nt];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int64_t u = blockIdx.x; u < total; u += gridDim.x) {
-    const int k = task_of(P.pre_cmp, nt, u);
-    const PackTask& T = P.tasks[k];
-    const int64_t s0 = (u - P.pre_cmp[k]) * PACK_CMP_SLOTS;
-    int64_t code[PACK_SLOTS_PER_THREAD];
-    uint64_t val[PACK_SLOTS_PER_THREAD];
-    uint64_t ball[PACK_SLOTS_PER_THREAD];
-    int64_t cnt = 0;
+      // nonzero sums (for fp64 both signed zeros are dropped) to the front of
+      // each wavefront's stretch, then out at slots taken from the task's counter
+      const int r0 = wave * PER * 64;
+      uint64_t kk[PER], vv[PER], ball[PER];
+      uint32_t cnt = 0;
 #pragma unroll
-    for (int q = 0; q < PACK_SLOTS_PER_THREAD; ++q) {
-      const int64_t s = s0 + (int64_t)q * PACK_BLOCK + threadIdx.x;
-      bool keep = false;
-      code[q] = 0;
-      val[q] = 0;
-      if (s < T.slots) {
-        if (T.direct) {
-          code[q] = s;
-          val[q] = T.table[s];
-          keep = true;
-        } else {
-          const uint64_t key = T.table[2 * s];
-          code[q] = (int64_t)key - 1;
-          val[q] = T.table[2 * s + 1];
-          keep = key != 0;
-        }
-        // a zero sum is dropped (for fp64 both signed zeros)
-        keep = keep && (T.f64 ? (val[q] << 1) != 0 : val[q] != 0);
+      for (int r = 0; r < PER; ++r) {
+        const int s = r0 + r * 64 + lane;
+        kk[r] = direct ? (uint64_t)s : keys[s];
+        vv[r] = vals[s];
+        ball[r] = __ballot(f64 ? (vv[r] << 1) != 0 : vv[r] != 0);
+        cnt += (uint32_t)__popcll(ball[r]);
       }
-      ball[q] = __ballot(keep);
-      cnt += __popcll(ball[q]);
-    }
-    if (lane == 0) s_wave[wave] = cnt;
-    __syncthreads();
-    int64_t tot = 0, pos = 0;
-    for (int w = 0; w < PACK_BLOCK / 64; ++w) {
-      if (w == wave) pos = tot;
-      tot += s_wave[w];
-    }
-    if (threadIdx.x == 0)
-      s_base = tot ? (int64_t)atomicAdd(T.count, (unsigned long long)tot) : 0;
-    __syncthreads();
-    const int64_t base = s_base;
-    const uint64_t lt = (1ull << lane) - 1;
-    const int nx = T.la.nx;
-    int64_t* oc = static_cast<int64_t*>(T.out_c);
+      if (lane == 0) s_cnt[wave] = cnt;
+      __syncthreads();
+      uint32_t tot = 0, before = 0;
 #pragma unroll
-    for (int q = 0; q < PACK_SLOTS_PER_THREAD; ++q) {
-      if (ball[q] & (1ull << lane)) {
-        const int64_t at = base + pos + __popcll(ball[q] & lt);
-        if (at < T.out_cap) {
-          uint64_t c = (uint64_t)code[q];
-          for (int v = 0; v < nx; ++v) T.out_x[at * nx + v] = decode_step_fast(T.la, v, c);
-          oc[at] = (int64_t)val[q];
-        }
+      for (int w = 0; w < NW; ++w) {
+        if (w < wave) before += s_cnt[w];
+        tot += s_cnt[w];
       }
-      pos += __popcll(ball[q]);
+      if (tid == 0)
+        s_base = tot ? (int64_t)atomicAdd(T.count, (unsigned long long)tot) : 0;
+      uint32_t pos = 0;
+#pragma unroll
+      for (int r = 0; r < PER; ++r) {
+        if (ball[r] & (1ull << lane)) {
+          const uint32_t at = r0 + pos + (uint32_t)__popcll(ball[r] & ((1ull << lane) - 1));
+          keys[at] = kk[r];
+          vals[at] = vv[r];
+        }
+        pos += (uint32_t)__popcll(ball[r]);
+      }
+      __syncthreads();
+      const int64_t out0 = s_base + before;
+      int32_t* ox = uniform_ptr(T.out_x);
+      int64_t* oc = uniform_ptr(static_cast<int64_t*>(T.out_c));
+      const int64_t cap = uniform(T.out_cap);
+      for (uint32_t t = lane; t < cnt; t += 64) {
+        const int64_t at = out0 + t;
+        if (at >= cap) break;
+        uint64_t c = (uint64_t)lo + keys[r0 + t];
+        for (int v = 0; v < nx; ++v) ox[at * nx + v] = pack_digit(s_dig[v], c);
+        oc[at] = (int64_t)vals[r0 + t];
+      }
+      __syncthreads();   // the next interval clears the table
     }
-    __syncthreads();   // s_wave and s_base are reused by the next unit
   }
 }
 
@@ -329,8 +634,7 @@ __global__ void __launch_bounds__(PACK_BLOCK) k_pack_post(void* table) {
 }  // namespace
 
 size_t pack_table_bytes(int max_tasks) {
-  return sizeof(PackHeader) + 3 * sizeof(int64_t) * ((size_t)max_tasks + 1) +
-         sizeof(PackTask) * (size_t)max_tasks;
+  return sizeof(PackHeader) + sizeof(PackTask) * (size_t)max_tasks;
 }
 
 hipError_t launch_pack_boxes(const int32_t* const* vals, const int64_t* n, const int32_t* nv,
@@ -341,10 +645,21 @@ hipError_t launch_pack_boxes(const int32_t* const* vals, const int64_t* n, const
   return hipGetLastError();
 }
 
-hipError_t launch_pack_run(void* table_dev, int grid, hipStream_t s) {
-  hipLaunchKernelGGL(k_pack_prep, dim3((unsigned)grid), dim3(PACK_BLOCK), 0, s, table_dev);
-  hipLaunchKernelGGL(k_pack_mul, dim3((unsigned)grid), dim3(PACK_BLOCK), 0, s, table_dev);
-  hipLaunchKernelGGL(k_pack_compact, dim3((unsigned)grid), dim3(PACK_BLOCK), 0, s, table_dev);
+hipError_t pack_setup() {   // once per context's device
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pack_sort),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)(PACK_BUCKETS * 4));
+}
+
+hipError_t launch_pack_run(void* table_dev, int max_tasks, int num_cu, hipStream_t s) {
+  const int tasks = std::min(2 * max_tasks, num_cu);
+  hipLaunchKernelGGL(k_pack_sort, dim3((unsigned)tasks), dim3(PACK_SORT_BLOCK),
+                     (size_t)PACK_BUCKETS * 4, s, table_dev);
+  hipLaunchKernelGGL(k_pack_count, dim3((unsigned)std::min(4 * max_tasks, num_cu) * 4),
+                     dim3(PACK_BLOCK), 0, s, table_dev);
+  hipLaunchKernelGGL(k_pack_plan, dim3((unsigned)std::min(max_tasks, num_cu)), dim3(PACK_BLOCK),
+                     0, s, table_dev);
+  hipLaunchKernelGGL(k_pack_mul, dim3((unsigned)(PACK_PER_CU * num_cu)), dim3(PACK_BLOCK), 0, s,
+                     table_dev);
   hipLaunchKernelGGL(k_pack_post, dim3(1), dim3(PACK_BLOCK), 0, s, table_dev);
   return hipGetLastError();
 }
