@@ -12,7 +12,13 @@
 //
 // Intervals: the code space is cut into cells of 2^cw codes; a counting pass
 // bounds the products of every cell, and a cell is cut into equal intervals of
-// about `target` products.
+// about `target` products.  Crowded columns (a box that an outlier makes huge)
+// are sorted within their buckets too, so that a row finds exactly the columns
+// of an interval, and the cells are then bounded by a sorted sample of the
+// products: 600 x 900 terms of three variables in [0, 24) and one outlier
+// each would otherwise be one workgroup's, 95 ms instead of 0.34 (0.50 through
+// the groups); 5,000 x 6,000 terms of five variables take 3.6 ms (139 through
+// the groups).
 //
 // Six launches in all (sort, place when a factor is large, count, plan,
 // multiply, finish) against eighteen of the range-grouped layout, which writes
@@ -36,7 +42,10 @@ constexpr int PLAN_BLOCK = 1024;
 constexpr uint32_t HASH_MUL = 0x9E3779B1u;  // odd, 2^32 / golden ratio
 constexpr uint32_t PART_MUL = 0x85EBCA6Bu;  // odd: the table's hash
 constexpr int MAX_PROBE = 256;
-constexpr int STACK = 72;
+// Intervals still to do: a cut leaves seven more, and at most twenty cuts lead
+// from 2^62 codes to the 64 that are not cut.
+constexpr int STACK = 144;
+constexpr int PARTS = 72;   // stretches still to do, one more per halving
 constexpr int ROWS = 1;     // rows per lane and batch
 constexpr int STEPS = 2;    // candidates per lane with their loads in flight
 
@@ -94,19 +103,35 @@ __device__ __forceinline__ void place_term(const DirectArgs& R, const DirectSet&
   }
 }
 
+// Term t of the crowded columns by bucket, to its place among the terms
+// [b0, b1) of its bucket.
+__device__ __forceinline__ void place_sorted(const DirectArgs& R, const DirectSet& S, int64_t t,
+                                             int32_t b0, int32_t b1) {
+  const int64_t k = R.tmp_k[t];
+  int32_t at = b0;
+#pragma unroll 4
+  for (int32_t o = b0; o < b1; ++o) {
+    const int64_t y = R.tmp_k[o];
+    at += y < k || (y == k && o < t) ? 1 : 0;
+  }
+  place_term(R, S, R.tmp_i[t], k, at);
+}
+
 // One workgroup per set: bucket histogram of its codes in LDS, each term's
 // rank in its bucket, bucket starts.  Sets of at most DIRECT_PLACE terms are
 // also placed here (one launch less; more terms than that are placed by many
 // workgroups, one compute unit being slow at scattered stores).  The first
 // workgroup clears the cells' counters.
 __global__ void __launch_bounds__(SORT_BLOCK) k_rd_sort(DirectArgs R) {
-  extern __shared__ int32_t hist[];
+  extern __shared__ __align__(8) int32_t hist[];
   __shared__ uint32_t s_ws[SORT_BLOCK / 64 + 1];
+  __shared__ unsigned long long s_sq;
+  if (threadIdx.x == 0) s_sq = 0;
   const DirectSet& S = R.set[blockIdx.x];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   for (int64_t k = tid; k < S.nbk; k += SORT_BLOCK) hist[k] = 0;
   if (blockIdx.x == 0)
-    for (int64_t k = tid; k < R.ncell; k += SORT_BLOCK) R.ccount[k] = 0;
+    for (int64_t k = tid; k < max(R.ncell, (int64_t)R.ncrowd); k += SORT_BLOCK) R.ccount[k] = 0;
   __syncthreads();
   uint32_t err = 0;
   uint64_t cmin = ~0ull, cmax = 0;   // sizes of the coefficients (fp64: of their bits)
@@ -123,11 +148,14 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_rd_sort(DirectArgs R) {
   const int64_t per = ((S.nbk + SORT_BLOCK - 1) / SORT_BLOCK) * 64;
   const int64_t b0 = min(S.nbk, wave * per), b1 = min(S.nbk, b0 + per);
   uint32_t sum = 0;
+  uint64_t sq = 0;
   for (int64_t b = b0; b < b1; b += 64) {
     const uint32_t v = b + lane < b1 ? (uint32_t)hist[b + lane] : 0u;
     sum += lane_value(wave_scan_add(v), 63);
+    sq += (uint64_t)v * v;
   }
   if (lane == 0) s_ws[wave] = sum;
+  if (blockIdx.x == 1 && sq) atomicAdd(&s_sq, (unsigned long long)sq);
   __syncthreads();
   uint32_t run = 0;
   for (int w = 0; w < wave; ++w) run += s_ws[w];
@@ -151,17 +179,42 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_rd_sort(DirectArgs R) {
   atomicMin(&s_min, (unsigned long long)cmin);
   atomicMax(&s_max, (unsigned long long)cmax);
   __syncthreads();
+  const bool crowd = blockIdx.x == 1 && s_sq > (uint64_t)CROWDED * (uint64_t)max(S.n, S.n * S.n / S.nbk);
   if (tid == 0) {
     R.meta->set_err[blockIdx.x] = err;
     R.meta->set_min[blockIdx.x] = s_min;
     R.meta->set_max[blockIdx.x] = s_max;
+    if (blockIdx.x == 1) R.meta->crowd = crowd ? 1u : 0u;
   }
   if (S.n <= DIRECT_PLACE) {
     for (int64_t i = tid; i < S.n; i += SORT_BLOCK) {
       const int64_t code = set_code(S, i, &err);
-      place_term(R, S, i, code, hist[code >> S.shift] + S.rank[i]);
+      const int64_t at = hist[code >> S.shift] + S.rank[i];
+      if (crowd) {
+        R.tmp_k[at] = code;
+        R.tmp_i[at] = (int32_t)i;
+      } else {
+        place_term(R, S, i, code, at);
+      }
     }
   }
+  if (!crowd) return;
+  __syncthreads();
+  if (S.n <= DIRECT_PLACE)
+    for (int64_t t = tid; t < S.n; t += SORT_BLOCK) {
+      const int64_t b = R.tmp_k[t] >> S.shift;
+      place_sorted(R, S, t, hist[b], b + 1 < S.nbk ? hist[b + 1] : (int32_t)S.n);
+    }
+  __syncthreads();   // hist has been read
+  int64_t* key = reinterpret_cast<int64_t*>(hist);
+  const DirectSet& A = R.set[0];
+  for (int o = tid; o < R.ncrowd; o += SORT_BLOCK)
+    key[o] = set_code(A, sample_of(o, 0, A.n), &err) +
+             set_code(S, sample_of(o, DIRECT_CROWD_CELLS, S.n), &err);
+  __syncthreads();
+  block_sort<SORT_BLOCK>(key, R.ncrowd);
+  for (int o = tid; o <= R.ncrowd; o += SORT_BLOCK)
+    R.bounds[o] = o == 0 ? 0 : o == R.ncrowd ? R.ncodes : key[o];
 }
 
 __global__ void __launch_bounds__(SMALL_BLOCK) k_rd_place(DirectArgs R) {
@@ -170,7 +223,48 @@ __global__ void __launch_bounds__(SMALL_BLOCK) k_rd_place(DirectArgs R) {
   if (i >= S.n || S.n <= DIRECT_PLACE) return;
   uint32_t err = 0;   // (reported by the sort)
   const int64_t code = set_code(S, i, &err);
-  place_term(R, S, i, code, S.start[code >> S.shift] + S.rank[i]);
+  const int64_t at = S.start[code >> S.shift] + S.rank[i];
+  if (blockIdx.y == 1 && R.meta->crowd) {
+    R.tmp_k[at] = code;
+    R.tmp_i[at] = (int32_t)i;
+  } else {
+    place_term(R, S, i, code, at);
+  }
+}
+
+// Crowded columns of more than DIRECT_PLACE terms, sorted (else nothing to do).
+__global__ void __launch_bounds__(SMALL_BLOCK) k_rd_order(DirectArgs R) {
+  if (!R.meta->crowd) return;
+  const DirectSet& S = R.set[1];
+  const int64_t t = (int64_t)blockIdx.x * SMALL_BLOCK + threadIdx.x;
+  if (t >= S.n || S.n <= DIRECT_PLACE) return;
+  const int64_t b = R.tmp_k[t] >> S.shift;
+  place_sorted(R, S, t, S.start[b], S.start[b + 1]);
+}
+
+// The columns of codes xlo .. xhi: exactly when they are crowded, else their
+// whole buckets (start[0] = 0 and start[nbk] = n close the ends).
+__device__ __forceinline__ uint32_t column_from(const DirectSet& B, uint32_t j0, uint32_t j1,
+                                                int64_t base, int64_t x) {
+  if (B.k64) return first_from(B.k64, j0, j1, x);
+  const uint32_t off = (uint32_t)(x - base);   // at most a bucket's 2^30 codes past base
+  while (j0 < j1) {
+    const uint32_t m = (j0 + j1) >> 1;
+    if (B.k32[m] - (uint32_t)base < off) j0 = m + 1;
+    else j1 = m;
+  }
+  return j0;
+}
+__device__ __forceinline__ void columns_of(const DirectSet& B, bool crowd, int64_t xlo,
+                                           int64_t xhi, uint32_t* j0, uint32_t* j1) {
+  const int64_t lo = max((int64_t)0, min(xlo, B.maxc)), hi = max((int64_t)0, min(xhi, B.maxc));
+  const int64_t q0 = lo >> B.shift, q1 = hi >> B.shift;
+  *j0 = (uint32_t)B.start[q0];
+  *j1 = (uint32_t)B.start[q1 + 1];
+  if (crowd) {
+    *j0 = column_from(B, *j0, (uint32_t)B.start[q0 + 1], q0 << B.shift, lo);
+    *j1 = column_from(B, (uint32_t)B.start[q1], *j1, q1 << B.shift, hi + 1);
+  }
 }
 
 // ------------------------------------------------------------ counting
@@ -179,36 +273,55 @@ __global__ void __launch_bounds__(SMALL_BLOCK) k_rd_place(DirectArgs R) {
 // are looked up once per cell boundary.
 __global__ void __launch_bounds__(SMALL_BLOCK) k_rd_count(DirectArgs R) {
   __shared__ unsigned long long s_sum[COUNT_CELLS];
-  const int64_t c0 = (int64_t)blockIdx.x * COUNT_CELLS;
   const int tid = threadIdx.x;
-  if (tid < COUNT_CELLS) s_sum[tid] = 0;
-  __syncthreads();
-  uint32_t cnt[COUNT_CELLS];
-#pragma unroll
-  for (int q = 0; q < COUNT_CELLS; ++q) cnt[q] = 0;
   const DirectSet& A = R.set[0];
   const DirectSet& B = R.set[1];
   const int64_t per = (A.n + gridDim.y - 1) / gridDim.y;
   const int64_t i0 = per * blockIdx.y, i1 = min(A.n, i0 + per);
-  for (int64_t i = i0 + tid; i < i1; i += SMALL_BLOCK) {
-    const int64_t x0 = (c0 << R.cw) - A.k64[i];   // lowest column code of the first cell
+  const bool crowd = R.meta->crowd != 0;
+  const int64_t cells = crowd ? R.ncrowd : R.ncell;
+  for (int64_t c0 = (int64_t)blockIdx.x * COUNT_CELLS; c0 < cells;
+       c0 += (int64_t)gridDim.x * COUNT_CELLS) {
+    if (tid < COUNT_CELLS) s_sum[tid] = 0;
+    __syncthreads();
+    uint32_t cnt[COUNT_CELLS];
+#pragma unroll
+    for (int q = 0; q < COUNT_CELLS; ++q) cnt[q] = 0;
+    if (crowd) {
+      for (int64_t i = i0 + tid; i < i1; i += SMALL_BLOCK) {
+        const int64_t a = A.k64[i];
+#pragma unroll
+        for (int q = 0; q < COUNT_CELLS; ++q) {
+          const int64_t lo = R.bounds[c0 + q] - a, hi = R.bounds[c0 + q + 1] - 1 - a;
+          if (hi < lo || hi < 0 || lo > B.maxc) continue;
+          uint32_t j0, j1;
+          columns_of(B, true, lo, hi, &j0, &j1);
+          cnt[q] += j1 - j0;
+        }
+      }
+    } else {
+      for (int64_t i = i0 + tid; i < i1; i += SMALL_BLOCK) {
+        const int64_t x0 = (c0 << R.cw) - A.k64[i];   // lowest column code of the first cell
+#pragma unroll
+        for (int q = 0; q < COUNT_CELLS; ++q) {
+          const int64_t lo = x0 + ((int64_t)q << R.cw), hi = lo + ((int64_t)1 << R.cw) - 1;
+          if (hi < 0 || lo > B.maxc) continue;
+          const int64_t j0 = lo <= 0 ? 0 : B.start[lo >> B.shift];
+          const int64_t j1 = hi >= B.maxc ? B.n : B.start[(hi >> B.shift) + 1];
+          cnt[q] += (uint32_t)(j1 - j0);
+        }
+      }
+    }
 #pragma unroll
     for (int q = 0; q < COUNT_CELLS; ++q) {
-      const int64_t lo = x0 + ((int64_t)q << R.cw), hi = lo + ((int64_t)1 << R.cw) - 1;
-      if (hi < 0 || lo > B.maxc) continue;
-      const int64_t j0 = lo <= 0 ? 0 : B.start[lo >> B.shift];
-      const int64_t j1 = hi >= B.maxc ? B.n : B.start[(hi >> B.shift) + 1];
-      cnt[q] += (uint32_t)(j1 - j0);
+      const uint32_t w = lane_value(wave_scan_add(cnt[q]), 63);
+      if ((tid & 63) == 0 && w) atomicAdd(&s_sum[q], (unsigned long long)w);
     }
+    __syncthreads();
+    if (tid < COUNT_CELLS && c0 + tid < cells && s_sum[tid])
+      atomicAdd(reinterpret_cast<unsigned long long*>(&R.ccount[c0 + tid]), s_sum[tid]);
+    __syncthreads();   // the next cells clear s_sum
   }
-#pragma unroll
-  for (int q = 0; q < COUNT_CELLS; ++q) {
-    const uint32_t w = lane_value(wave_scan_add(cnt[q]), 63);
-    if ((tid & 63) == 0 && w) atomicAdd(&s_sum[q], (unsigned long long)w);
-  }
-  __syncthreads();
-  if (tid < COUNT_CELLS && c0 + tid < R.ncell && s_sum[tid])
-    atomicAdd(reinterpret_cast<unsigned long long*>(&R.ccount[c0 + tid]), s_sum[tid]);
 }
 
 // Every workgroup scans the cells' interval counts and writes the intervals
@@ -216,8 +329,10 @@ __global__ void __launch_bounds__(SMALL_BLOCK) k_rd_count(DirectArgs R) {
 __global__ void __launch_bounds__(PLAN_BLOCK) k_rd_plan(DirectArgs R) {
   __shared__ int64_t s_ws[PLAN_BLOCK / 64 + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t per = (R.ncell + PLAN_BLOCK - 1) / PLAN_BLOCK;
-  const int64_t c0 = min(R.ncell, tid * per), c1 = min(R.ncell, c0 + per);
+  const bool crowd = R.meta->crowd != 0;
+  const int64_t cells = crowd ? R.ncrowd : R.ncell;
+  const int64_t per = (cells + PLAN_BLOCK - 1) / PLAN_BLOCK;
+  const int64_t c0 = min(cells, tid * per), c1 = min(cells, c0 + per);
   const auto block_total = [&](int64_t v) -> int64_t {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
     __syncthreads();
@@ -230,13 +345,28 @@ __global__ void __launch_bounds__(PLAN_BLOCK) k_rd_plan(DirectArgs R) {
   int64_t local = 0;
   for (int64_t c = c0; c < c1; ++c) local += R.ccount[c];
   const int64_t all = block_total(local);
-  // sum of ceil(count / t) <= cells + all / t, kept within the array
-  const int64_t room = max((int64_t)1, R.max_units - R.ncell);
+  // sum of ceil(count / t) <= cells + all / t, kept within the array; sampled
+  // cells are also cut at 2^31 codes when offsets are 32-bit, at most once per
+  // cell of equal width
+  const int64_t room = max((int64_t)1, crowd ? R.max_units - cells - R.ncell : R.grid - cells);
   const int64_t t = max(R.target, (all + room - 1) / room);
+  const auto cell_of = [&](int64_t c, int64_t* lo, int64_t* hi) {
+    if (crowd) {
+      *lo = R.bounds[c];
+      *hi = R.bounds[c + 1];
+    } else {
+      *lo = c << R.cw;
+      *hi = min(R.ncodes, *lo + ((int64_t)1 << R.cw));
+    }
+  };
   const auto units_of = [&](int64_t c) -> int64_t {
     const int64_t n = R.ccount[c];
-    const int64_t k = n ? (n + t - 1) / t : 0;
-    return min(k, (int64_t)1 << R.cw);
+    int64_t k = n ? (n + t - 1) / t : 0;
+    if (!crowd || k == 0) return min(k, (int64_t)1 << R.cw);
+    int64_t lo, hi;
+    cell_of(c, &lo, &hi);
+    if (!R.wide_codes) k = max(k, (hi - lo + ((int64_t)1 << 31) - 1) >> 31);
+    return min(k, hi - lo);
   };
   int64_t mine = 0;
   for (int64_t c = c0; c < c1; ++c) mine += units_of(c);
@@ -257,7 +387,8 @@ __global__ void __launch_bounds__(PLAN_BLOCK) k_rd_plan(DirectArgs R) {
   for (int64_t c = c0; c < c1; ++c) {
     const int64_t k = units_of(c);
     if (c % gridDim.x == blockIdx.x && k > 0) {
-      const int64_t lo = c << R.cw, hi = min(R.ncodes, lo + ((int64_t)1 << R.cw));
+      int64_t lo, hi;
+      cell_of(c, &lo, &hi);
       const int64_t step = (hi - lo + k - 1) / k;
       for (int64_t u = 0; u < k; ++u) {
         const int64_t a = min(hi, lo + u * step), z = min(hi, a + step);
@@ -411,7 +542,9 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
   constexpr int NW = NT / 64, PER = SLOTS / NT, W = sizeof(T) / 8, WORDS = 1 << (MLOG - 5);
   constexpr bool WIDE = sizeof(K) == 8;
   constexpr K NONE = ~K(0);
-  constexpr uint32_t CROWD = (1u << MLOG) / 4;   // products of an interval that is cut
+  // products of an interval that is cut; fewer when its codes crowd, since
+  // those that share cells must then fit the table
+  constexpr uint32_t CROWD = (1u << MLOG) / 4, CROWD_FEW = (1u << MLOG) / 9;
   static_assert(SLOTS % NT == 0, "each wavefront owns a stretch of the table");
   static_assert(WORDS % NT == 0, "each thread owns words of the marks");
   __shared__ uint32_t marked[WORDS], shared[WORDS];
@@ -428,17 +561,15 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
   __shared__ uint32_t s_next;             // rows handed out
   __shared__ int64_t s_lo[STACK];         // intervals still to do
   __shared__ K s_width[STACK];
-  __shared__ K p_lo[STACK], p_hi[STACK];   // stretches of the shared products
+  __shared__ K s_sample[64];              // offsets of products, when the columns are crowded
+  __shared__ K p_lo[PARTS], p_hi[PARTS];   // stretches of the shared products
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if ((int64_t)blockIdx.x >= R.meta->nbins) return;
-  int64_t lo;
-  K width;
-  {
-    const longlong2 unit = R.units[blockIdx.x];
-    lo = uniform((int64_t)unit.x);
-    width = uniform((K)unit.y);          // codes of the interval
-  }
-  if (width == 0) return;
+  const int64_t units = uniform(R.meta->nbins);
+  if ((int64_t)blockIdx.x >= units) return;
+  const bool crowd = uniform(R.meta->crowd) != 0;
+  const uint32_t most = crowd ? CROWD_FEW : CROWD;
+  int64_t lo = 0;
+  K width = 0;   // codes of the interval
   const bool stats = R.stats != nullptr;
   const bool zeros = uniform(R.meta->zeros) != 0;   // a product of two terms may be zero
   T* out_c = static_cast<T*>(R.out_c);
@@ -533,8 +664,10 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
   // The products whose offsets in the interval lie in [w0, w1), 64 per
   // wavefront and step.  PASS 0 marks, PASS 1 writes the terms alone in their
   // cells and (when `add`) adds the others, PASS 2 adds the others.
-  const auto walk = [&](auto pass, K w0, K w1, bool add) {
+  const auto walk_as = [&](auto pass, auto crowded, K w0, K w1, bool add) {
     constexpr int PASS = decltype(pass)::value;
+    constexpr bool CROWDS = decltype(crowded)::value;
+    constexpr uint32_t MOST = CROWDS ? CROWD_FEW : CROWD;
     const int64_t out0 = uniform(s_base);
     const DirectSet& A = R.set[0];
     const DirectSet& B = R.set[1];
@@ -555,7 +688,7 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
         if (lane == 0) bt = atomicAdd(&s_next, (uint32_t)(ROWS * 64));
         const uint32_t ib = i0 + lane_value(bt, 0);
         if (ib >= i1) break;
-        if (PASS == 0 && *(volatile uint32_t*)&s_products > CROWD && width > 64) return;
+        if (PASS == 0 && *(volatile uint32_t*)&s_products > MOST && width > 64) return;
         if (PASS == 2 && *(volatile uint32_t*)&s_over) return;
         int64_t a[ROWS];
         uint32_t cnt[ROWS], excl[ROWS];
@@ -565,12 +698,8 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
         for (int u = 0; u < ROWS; ++u) {
           const int64_t xlo = blo - a[u], xhi = bhi - a[u];
           const bool in = ib + u * 64 + lane < i1 && xhi >= 0 && xlo <= B.maxc;
-          // (start[0] = 0 and start[nbk] = n close the ends)
-          const uint32_t q0 = (uint32_t)(max((int64_t)0, min(xlo, B.maxc)) >> B.shift);
-          const uint32_t q1 = (uint32_t)(max((int64_t)0, min(xhi, B.maxc)) >> B.shift) + 1;
-          excl[u] = (uint32_t)B.start[q0];
-          cnt[u] = (uint32_t)B.start[q1] - excl[u];
-          if (!in) cnt[u] = 0;
+          columns_of(B, CROWDS, xlo, xhi, &excl[u], &cnt[u]);
+          cnt[u] = in ? cnt[u] - excl[u] : 0;
         }
         uint32_t total = 0;
 #pragma unroll
@@ -637,7 +766,10 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
             const uint32_t h = mix(key), cell = h >> (32 - MLOG);
             const uint32_t bit = 1u << (cell & 31);
             if (PASS == 0) {
-              products += (uint32_t)__popcll(__ballot(ok));
+              const uint64_t oks = __ballot(ok);
+              products += (uint32_t)__popcll(oks);
+              if (CROWDS && oks && lane == (int)__builtin_ctzll(oks))
+                s_sample[(wave + NW * (products >> 6)) & 63] = key;
               if (ok && (atomicOr(&marked[cell >> 5], bit) & bit)) atomicOr(&shared[cell >> 5], bit);
               continue;
             }
@@ -658,6 +790,10 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
         if (PASS == 0 && lane == 0) atomicAdd(&s_products, products);
       }
     }
+  };
+  const auto walk = [&](auto pass, K w0, K w1, bool add) {
+    if (crowd) walk_as(pass, std::true_type{}, w0, w1, add);
+    else walk_as(pass, std::false_type{}, w0, w1, add);
   };
   const auto clear_table = [&]() {
 #pragma unroll
@@ -738,15 +874,21 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
     }
   };
 
+  // (the grid has an interval per workgroup unless the columns are crowded)
+  for (int64_t unit = blockIdx.x; unit < units; unit += gridDim.x) {
   if (tid == 0) {
-    s_lo[0] = lo;
-    s_width[0] = width;
+    s_lo[0] = R.units[unit].x;
+    s_width[0] = (K)R.units[unit].y;
   }
   __syncthreads();
   for (int sp = 1; sp > 0;) {
     --sp;
     lo = uniform(s_lo[sp]);
     width = uniform(s_width[sp]);
+    if (width == 0) {
+      __syncthreads();   // the next interval's start is written
+      continue;
+    }
     if (R.ndig > 0) {
       const uint64_t c = (uint64_t)lo;
       U.start = c;
@@ -761,17 +903,33 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
     clear_table();
     if (tid == 0) s_next = 0;
     if (tid == 0) s_cursor = s_products = 0;
+    if (tid < 64) s_sample[tid] = NONE;
     __syncthreads();
     walk(std::integral_constant<int, 0>{}, 0, width, false);
     __syncthreads();
     const uint32_t products = uniform(s_products);
-    if (products > CROWD && width > 64) {   // the same for every thread
-      const K step = (width + 7) / 8;
-      if (tid < 8) {
-        const K w0 = min(width, (K)tid * step);
-        s_lo[sp + tid] = lo + w0;
-        s_width[sp + tid] = min(step, width - w0);
+    if (products > most && width > 64) {   // the same for every thread
+      if (wave == 0) {
+        // into equal parts, or at the octiles of sampled products: codes that
+        // crowd on several scales would take a cut per scale
+        const K key = s_sample[lane];
+        int rank = 0;
+#pragma unroll 8
+        for (int o = 0; o < 64; ++o) {
+          const K y = s_sample[o];
+          rank += y < key || (y == key && o < lane) ? 1 : 0;
+        }
+        const int n = (int)__popcll(__ballot(key != NONE));
+        const bool few = n < 32;
+        const K step = width / 8;   // (width > 64)
+        const int piece = few ? lane : rank / (n / 8);
+        if (lane == 0) s_lo[sp] = lo;
+        if (few ? lane > 0 && lane < 8 : key != NONE && rank > 0 && rank % (n / 8) == 0 && piece < 8)
+          s_lo[sp + piece] = lo + (int64_t)(few ? step * (K)lane : key);
       }
+      __syncthreads();
+      if (tid < 8)
+        s_width[sp + tid] = (K)((tid < 7 ? s_lo[sp + tid + 1] : lo + (int64_t)width) - s_lo[sp + tid]);
       sp += 8;
       __syncthreads();
       continue;
@@ -828,6 +986,7 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
       }
     }
   }
+  }
   if (stats) {
     for (int off = 32; off > 0; off >>= 1) {
       ins += __shfl_xor(ins, off);
@@ -859,7 +1018,7 @@ __global__ void k_rd_finish(const Meta* m, int64_t out_cap, int64_t* out_n, uint
 
 template <typename T, typename K, int NT, int MLOG, int SLOTS>
 void launch_mul(const DirectArgs& R, hipStream_t s) {
-  hipLaunchKernelGGL((k_rd_mul<T, K, NT, MLOG, SLOTS>), dim3((unsigned)R.max_units), dim3(NT), 0, s,
+  hipLaunchKernelGGL((k_rd_mul<T, K, NT, MLOG, SLOTS>), dim3((unsigned)R.grid), dim3(NT), 0, s,
                      R);
 }
 
@@ -892,20 +1051,24 @@ hipError_t launch_direct(const DirectArgs& R, kp_dtype dt, int64_t* out_n, uint3
   hipError_t e = direct_setup();
   if (e != hipSuccess) return e;
   if (R.ev0) (void)hipEventRecord(R.ev0, s);
-  const int64_t nbk = std::max(R.set[0].nbk, R.set[1].nbk);
+  const int64_t lds = std::max({R.set[0].nbk * 4, R.set[1].nbk * 4, (int64_t)R.ncrowd * 8});
   const int64_t rows = R.set[0].n, n = std::max(rows, R.set[1].n);
-  hipLaunchKernelGGL(k_rd_sort, dim3(2), dim3(SORT_BLOCK), (size_t)nbk * 4, s, R);
-  if (n > DIRECT_PLACE)
-    hipLaunchKernelGGL(k_rd_place, dim3((unsigned)((n + SMALL_BLOCK - 1) / SMALL_BLOCK), 2),
-                       dim3(SMALL_BLOCK), 0, s, R);
+  hipLaunchKernelGGL(k_rd_sort, dim3(2), dim3(SORT_BLOCK), (size_t)lds, s, R);
+  if (n > DIRECT_PLACE) {
+    const unsigned blocks = (unsigned)((n + SMALL_BLOCK - 1) / SMALL_BLOCK);
+    hipLaunchKernelGGL(k_rd_place, dim3(blocks, 2), dim3(SMALL_BLOCK), 0, s, R);
+    hipLaunchKernelGGL(k_rd_order, dim3(blocks), dim3(SMALL_BLOCK), 0, s, R);
+  }
   const int64_t groups = (R.ncell + COUNT_CELLS - 1) / COUNT_CELLS;
   // enough row slices for about 2048 counting workgroups, of at least 256 rows
   int64_t ys = (2048 + groups - 1) / groups;
   const int64_t most = (rows + SMALL_BLOCK - 1) / SMALL_BLOCK;
   ys = ys > most ? most : ys;
-  hipLaunchKernelGGL(k_rd_count, dim3((unsigned)groups, (unsigned)(ys > 0 ? ys : 1)),
-                     dim3(SMALL_BLOCK), 0, s, R);
-  const int64_t pg = R.max_units / 2048 + 1;
+  ys = ys > 0 ? ys : 1;
+  // crowded columns have more cells; the workgroups for them end at once otherwise
+  const int64_t xs = std::max(groups, std::min<int64_t>(R.ncrowd / COUNT_CELLS, 2048 / ys));
+  hipLaunchKernelGGL(k_rd_count, dim3((unsigned)xs, (unsigned)ys), dim3(SMALL_BLOCK), 0, s, R);
+  const int64_t pg = R.grid / 2048 + 1;
   hipLaunchKernelGGL(k_rd_plan, dim3((unsigned)(pg > 64 ? 64 : pg)), dim3(PLAN_BLOCK), 0, s, R);
   if (dt == KP_F64) launch_mul_typed<double, 4096, 1024, 3072>(R, s);
   else if (dt == KP_I128) launch_mul_typed<I128, 2048, 512, 2048>(R, s);
