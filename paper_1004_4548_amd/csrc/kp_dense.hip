@@ -28,6 +28,9 @@
 // per range instead of 63.  The edge test is one
 // unsigned min that sends an out-of-window pair to a per-lane discard slot.
 //
+// fp64 products of many pairs sort each bucket's terms too (order, after
+// scatter) and carry sums from row to row: see chain_step.
+//
 // Launches (one stream):
 //  1. prep    -- two workgroups, one per factor: bucket histogram of the codes
 //                in LDS (buckets of 2^shift codes) with each term's rank in
@@ -211,6 +214,7 @@ struct PrepArgs {
   PrepSeg seg[2];
   Meta* meta;
   int is_i64;
+  int order;              // the terms of a bucket are sorted afterwards
 };
 
 // Bucket of a code (codes outside the factor's box are flagged by the caller
@@ -322,6 +326,10 @@ __global__ void __launch_bounds__(PREP_BLOCK) k_dense_prep(PrepArgs args) {
 }
 
 constexpr int SCATTER_BLOCK = 256;
+// Pairs from which fp64 products sort their terms completely and carry sums
+// from row to row: the sort takes 10 to 18 us, and at this many pairs the sums
+// save about 25.
+constexpr int64_t DENSE_CHAIN_PAIRS = (int64_t)1 << 27;
 
 // Writes every term at its bucket-sorted position; for factor B also the
 // code range of each tile of 16 consecutive sorted terms.
@@ -335,10 +343,66 @@ __global__ void __launch_bounds__(SCATTER_BLOCK) k_dense_scatter(PrepArgs args, 
   sg.out_pk[pos] = (uint64_t)(uint32_t)k | ((uint64_t)(uint32_t)c << 32);
   sg.out_coef[pos] = (uint64_t)c;
   if (sg.deg_out) sg.deg_out[pos] = sg.deg_in[i];
-  if (isB) {
+  if (isB && !args.order) {
     const int64_t t = pos / DENSE_TILE, code = (int64_t)(uint32_t)k;
     __hip_atomic_fetch_min(&sg.tmin[t], code, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_fetch_max(&sg.tmax[t], code, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// Sorts the terms of every bucket by code, one wavefront per bucket, in place
+// (a bucket of more than ORDER_MAX terms stays as it is), and takes the tiles'
+// code ranges.
+constexpr int ORDER_MAX = 256;
+
+__global__ void __launch_bounds__(SCATTER_BLOCK) k_dense_order(PrepArgs args, int64_t blocksA) {
+  constexpr int NW = SCATTER_BLOCK / 64, PER = ORDER_MAX / 64;
+  __shared__ uint32_t s_code[NW][ORDER_MAX];
+  const bool isB = blockIdx.x >= blocksA;
+  const PrepSeg& sg = isB ? args.seg[1] : args.seg[0];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t b = (int64_t)(isB ? blockIdx.x - blocksA : blockIdx.x) * NW + wave;
+  if (b >= sg.nbk) return;
+  const int64_t s = sg.bstart[b];
+  const int n = (int)(sg.bstart[b + 1] - s);
+  if (n <= 0) return;
+  const auto tile = [&](int64_t pos, uint32_t code) {
+    if (!isB) return;
+    __hip_atomic_fetch_min(&sg.tmin[pos / DENSE_TILE], (int64_t)code, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_max(&sg.tmax[pos / DENSE_TILE], (int64_t)code, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+  };
+  if (n > ORDER_MAX) {
+    for (int i = lane; i < n; i += 64) tile(s + i, (uint32_t)sg.out_pk[s + i]);
+    return;
+  }
+  uint64_t pk[PER], c[PER];
+  int at[PER];
+#pragma unroll
+  for (int r = 0; r < PER; ++r) {
+    const int i = r * 64 + lane;
+    pk[r] = i < n ? sg.out_pk[s + i] : 0;
+    c[r] = i < n ? sg.out_coef[s + i] : 0;
+    s_code[wave][i] = (uint32_t)pk[r];
+    at[r] = 0;
+  }
+  wave_sync();
+  for (int o = 0; o < n; ++o) {
+    const uint32_t y = s_code[wave][o];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+      const uint32_t k = (uint32_t)pk[r];
+      at[r] += y < k || (y == k && o < r * 64 + lane) ? 1 : 0;
+    }
+  }
+  wave_sync();   // every term has been read
+#pragma unroll
+  for (int r = 0; r < PER; ++r) {
+    if (r * 64 + lane >= n) continue;
+    sg.out_pk[s + at[r]] = pk[r];
+    sg.out_coef[s + at[r]] = c[r];
+    tile(s + at[r], (uint32_t)pk[r]);
   }
 }
 
@@ -809,6 +873,7 @@ struct MulArgs {
   int64_t* ccount;
   const int32_t* a_sa;   // optional truncation: slack of each row of A (sorted order)
   const int32_t* b_tb;   // and degree of each term of B; a pair is kept iff tb <= sa
+  int chain;             // the terms are sorted: sums are carried from row to row
 };
 
 template <int U>
@@ -887,6 +952,74 @@ __device__ __forceinline__ void item_steps(std::integer_sequence<int, U...>, uin
                                            uint32_t off8, uint32_t lim, uint32_t base,
                                            const Coef<T, MUL>& c, uint32_t sa, int32_t tb) {
   (pair_step<T, MUL, EDGE, TRUNC, G + U>(a8, off8, lim, base, c, sa, tb), ...);
+}
+
+// fp64 sums carried from row to row.  The factors of a dense product have runs
+// of consecutive codes, so row u against term v mostly lands in the slot of row
+// u + 1 against term v - 1: the lane's sum then moves to the lane before it
+// (one DPP step) instead of being added in LDS, and only sums that no pair of
+// the next row continues are.  What bounds the plain steps is bank conflicts:
+// an fp64 add of 64 pairs that fall anywhere takes 24 clocks, of 64 in distinct
+// banks 9.  Three lanes in ten are left to add for four variables up to degree
+// 30 (runs of 8.5 terms); the step is then bound by its twelve vector
+// instructions: 46,376 x 46,376 terms in 1.11 ms instead of 1.49.  Integer adds
+// conflict less (7 clocks at best) and their steps are shorter: 10,000 x 10,000
+// int64 terms took 62 us instead of 50 this way, 128-bit sums 264 instead of
+// 189, so those kinds keep the plain steps.
+template <int CTRL>
+__device__ __forceinline__ uint32_t row_move(uint32_t v) {   // lanes without a source read 0
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL>
+__device__ __forceinline__ double row_move(uint32_t lo, uint32_t hi) {
+  return __longlong_as_double(
+      (long long)(((uint64_t)row_move<CTRL>(hi) << 32) | row_move<CTRL>(lo)));
+}
+
+struct Chain {
+  uint32_t rel;   // slot (byte offset in the window) of the lane's sum
+  double sum;
+};
+
+// One row; the lane's last sum moves on or is added in LDS.
+template <bool EDGE, int U>
+__device__ __forceinline__ void chain_step(uint32_t a8, uint32_t off8, uint32_t lim, uint32_t base,
+                                           const Coef<double, 3>& c, Chain& h) {
+  uint32_t rel = bcast16<U>(a8) + off8;
+  if (EDGE) rel = min(rel, lim);
+  double carry = 0;
+  if constexpr (U > 0) {
+    // the lane before this one continues this lane's sum (lane 0 of a row has
+    // none before it, so that no bit of `taken >> 1` crosses rows)
+    const uint64_t taken = __builtin_amdgcn_ballot_w64(row_move<0x111>(rel) == h.rel) &   // row_shr:1
+                           0xFFFEFFFEFFFEFFFEull;
+    const uint64_t bits = (uint64_t)__double_as_longlong(h.sum);
+    const double next = row_move<0x101>((uint32_t)bits, (uint32_t)(bits >> 32));          // row_shl:1
+    if (__builtin_amdgcn_inverse_ballot_w64(taken >> 1)) carry = next;
+    if (__builtin_amdgcn_inverse_ballot_w64(~taken)) lds_add(h.rel + base, h.sum);
+  }
+  h.rel = rel;
+  h.sum = __builtin_fma(row_move<0x150 + U>(c.lo, c.hi), c.bw, carry);                    // row_newbcast:U
+}
+
+template <bool EDGE, int G, int... U>
+__device__ __forceinline__ void chain_steps(std::integer_sequence<int, U...>, uint32_t a8,
+                                            uint32_t off8, uint32_t lim, uint32_t base,
+                                            const Coef<double, 3>& c, Chain& h) {
+  (chain_step<EDGE, G + U>(a8, off8, lim, base, c, h), ...);
+}
+
+// The R rows (4, 8, 12 or 16) of a lane group, and the sums left at the end.
+template <bool EDGE>
+__device__ __forceinline__ void chain_item(uint32_t a8, uint32_t off8, uint32_t lim, uint32_t base,
+                                           const Coef<double, 3>& c, int R) {
+  constexpr auto q4 = std::make_integer_sequence<int, 4>{};
+  Chain h{};
+  chain_steps<EDGE, 0>(q4, a8, off8, lim, base, c, h);
+  if (R > 4) chain_steps<EDGE, 4>(q4, a8, off8, lim, base, c, h);
+  if (R > 8) chain_steps<EDGE, 8>(q4, a8, off8, lim, base, c, h);
+  if (R > 12) chain_steps<EDGE, 12>(q4, a8, off8, lim, base, c, h);
+  lds_add(h.rel + base, h.sum);
 }
 
 // 128-bit slots (MUL 5): the low word's offset is computed as for the other
@@ -1008,7 +1141,7 @@ __device__ __forceinline__ int32_t row_min16(int32_t v) {
   return min(v, row_ror<8>(v));
 }
 
-template <typename T, int MUL, bool TRUNC>
+template <typename T, int MUL, bool TRUNC, bool CHAIN>
 __device__ __forceinline__ void run_item(const ItemRegs& x, int64_t L, uint32_t lim, int lane,
                                          int64_t nb, uint32_t base, uint32_t hi8) {
   // a truncated product skips an item whose every pair is over the degree
@@ -1021,7 +1154,12 @@ __device__ __forceinline__ void run_item(const ItemRegs& x, int64_t L, uint32_t 
   const int R = item_instr(x.n);   // wavefront-uniform
   const uint32_t a8 = (lane & 15) < R && R * (lane >> 4) + (lane & 15) < x.n
                           ? ((uint32_t)x.a << 3) : ROW_SENTINEL;
-  if constexpr (MUL == 5) {
+  if constexpr (CHAIN) {
+    Coef<double, 3> c{(uint32_t)x.ac, (uint32_t)(x.ac >> 32), 0, 0.0};
+    __builtin_memcpy(&c.bw, &x.bc, 8);
+    if (x.core) chain_item<false>(a8, off8, lim, base, c, 16);
+    else chain_item<true>(a8, off8, lim, base, c, R);
+  } else if constexpr (MUL == 5) {
     const uint32_t clo = (uint32_t)x.ac, chi = (uint32_t)(x.ac >> 32);
     const int64_t bw = (int64_t)x.bc;
     if (x.core)
@@ -1058,7 +1196,7 @@ __device__ __forceinline__ void run_item(const ItemRegs& x, int64_t L, uint32_t 
 
 // Items [ib, ie) of the task, wavefront w taking ib + w, ib + w + NW, ...;
 // the next item's rows and terms are loaded while the current one runs.
-template <typename T, int MUL, int BS, bool TRUNC>
+template <typename T, int MUL, int BS, bool TRUNC, bool CHAIN>
 __device__ __forceinline__ void run_items(const MulArgs& M, int64_t ib, int64_t ie, int64_t L,
                                           uint32_t S8, uint32_t base, uint32_t hi8) {
   constexpr int NW = BS / 64;
@@ -1078,11 +1216,11 @@ __device__ __forceinline__ void run_items(const MulArgs& M, int64_t ib, int64_t 
     fetch_item<WIDE, TRUNC>(M, readlane64(dv, 0), lane, x0);
     for (int k = 0; k + 1 < cnt; k += 2) {
       fetch_item<WIDE, TRUNC>(M, readlane64(dv, k + 1), lane, x1);
-      run_item<T, MUL, TRUNC>(x0, L, lim, lane, M.nb, base, hi8);
+      run_item<T, MUL, TRUNC, CHAIN>(x0, L, lim, lane, M.nb, base, hi8);
       fetch_item<WIDE, TRUNC>(M, readlane64(dv, min(k + 2, cnt - 1)), lane, x0);
-      run_item<T, MUL, TRUNC>(x1, L, lim, lane, M.nb, base, hi8);
+      run_item<T, MUL, TRUNC, CHAIN>(x1, L, lim, lane, M.nb, base, hi8);
     }
-    if (cnt & 1) run_item<T, MUL, TRUNC>(x0, L, lim, lane, M.nb, base, hi8);
+    if (cnt & 1) run_item<T, MUL, TRUNC, CHAIN>(x0, L, lim, lane, M.nb, base, hi8);
   }
 }
 
@@ -1179,19 +1317,20 @@ __global__ void __launch_bounds__(BS) k_dense_mul(MulArgs M) {
     const int64_t hw = Sw + DENSE_DUMMY;
     const uint32_t hi8 = (uint32_t)(hw * 8);
     if constexpr (std::is_same<T, double>::value) {
-      if (trunc) run_items<T, 3, BS, true>(M, pb, pe, L, S8, base, hi8);
-      else run_items<T, 3, BS, false>(M, pb, pe, L, S8, base, hi8);
+      if (trunc) run_items<T, 3, BS, true, false>(M, pb, pe, L, S8, base, hi8);
+      else if (M.chain) run_items<T, 3, BS, false, true>(M, pb, pe, L, S8, base, hi8);
+      else run_items<T, 3, BS, false, false>(M, pb, pe, L, S8, base, hi8);
     } else if constexpr (std::is_same<T, I128>::value) {
-      if (trunc) run_items<T, 5, BS, true>(M, pb, pe, L, S8, base, hi8);
-      else run_items<T, 5, BS, false>(M, pb, pe, L, S8, base, hi8);
+      if (trunc) run_items<T, 5, BS, true, false>(M, pb, pe, L, S8, base, hi8);
+      else run_items<T, 5, BS, false, false>(M, pb, pe, L, S8, base, hi8);
     } else if (trunc) {   // truncated products: the narrowest kind, or general int64
-      if (narrow & 4u) run_items<T, 4, BS, true>(M, pb, pe, L, S8, base, hi8);
-      else run_items<T, 0, BS, true>(M, pb, pe, L, S8, base, hi8);
+      if (narrow & 4u) run_items<T, 4, BS, true, false>(M, pb, pe, L, S8, base, hi8);
+      else run_items<T, 0, BS, true, false>(M, pb, pe, L, S8, base, hi8);
     } else {
-      if (narrow & 4u) run_items<T, 4, BS, false>(M, pb, pe, L, S8, base, hi8);
-      else if (narrow & 2u) run_items<T, 2, BS, false>(M, pb, pe, L, S8, base, hi8);
-      else if (narrow & 1u) run_items<T, 1, BS, false>(M, pb, pe, L, S8, base, hi8);
-      else run_items<T, 0, BS, false>(M, pb, pe, L, S8, base, hi8);
+      if (narrow & 4u) run_items<T, 4, BS, false, false>(M, pb, pe, L, S8, base, hi8);
+      else if (narrow & 2u) run_items<T, 2, BS, false, false>(M, pb, pe, L, S8, base, hi8);
+      else if (narrow & 1u) run_items<T, 1, BS, false, false>(M, pb, pe, L, S8, base, hi8);
+      else run_items<T, 0, BS, false, false>(M, pb, pe, L, S8, base, hi8);
     }
     __syncthreads();
     flush_window<T, BS>(M, smem_raw, L, Sw, hw, !M.accumulate && pb == wb && pe == we);
@@ -1447,12 +1586,20 @@ hipError_t launch_dense_laurent(const DensePlan& P, const DenseBufs& B, kp_dtype
                       B.rank_b, B.bstartB, B.tmin, B.tmax, B.ccount, P.nchunk, B.b_tb_in, B.b_tb};
   pa.meta = B.meta;
   pa.is_i64 = dt != KP_F64;
+  const bool chain = dt == KP_F64 && !B.a_sa_in &&
+                     (double)B.na * (double)B.nb >= (double)DENSE_CHAIN_PAIRS;
+  pa.order = chain ? 1 : 0;
   const size_t hist_bytes = (size_t)std::max(P.nbkA, P.nbkB) * 4;
   hipLaunchKernelGGL(k_dense_prep, dim3(2), dim3(PREP_BLOCK), hist_bytes, s, pa);
   const int64_t blocksA = (B.na + SCATTER_BLOCK - 1) / SCATTER_BLOCK;
   const int64_t blocksB = (B.nb + SCATTER_BLOCK - 1) / SCATTER_BLOCK;
   hipLaunchKernelGGL(k_dense_scatter, dim3((unsigned)(blocksA + blocksB)), dim3(SCATTER_BLOCK), 0,
                      s, pa, blocksA);
+  if (chain) {
+    constexpr int NW = SCATTER_BLOCK / 64;
+    const int64_t oa = (P.nbkA + NW - 1) / NW, ob = (P.nbkB + NW - 1) / NW;
+    hipLaunchKernelGGL(k_dense_order, dim3((unsigned)(oa + ob)), dim3(SCATTER_BLOCK), 0, s, pa, oa);
+  }
 
   PlanArgs pl{P.S, P.nwin, P.ntiles, P.nkeys, B.nb, P.target_tasks, P.min_work, P.items_cap,
               ITEMS_LDS_BYTES, P.accumulate,
@@ -1465,7 +1612,7 @@ hipError_t launch_dense_laurent(const DensePlan& P, const DenseBufs& B, kp_dtype
   const int64_t W1 = P.nwin + 1;
   MulArgs ma{B.meta, B.apk, B.ac, B.bpk, B.bc, B.nb, P.S, P.nwin, P.nkeys, B.items, B.task_w,
              B.task_begin, B.win + W_IBASE * W1, P.accumulate, B.dense, B.stage_k, B.stage_c,
-             B.ccount, B.a_sa_in ? B.a_sa : nullptr, B.b_tb_in ? B.b_tb : nullptr};
+             B.ccount, B.a_sa_in ? B.a_sa : nullptr, B.b_tb_in ? B.b_tb : nullptr, chain ? 1 : 0};
   const size_t lds = (size_t)(P.S + DENSE_DUMMY) * 8 * coef_words(dt);
   const unsigned grid = (unsigned)P.max_tasks;
   if (B.ev0) (void)hipEventRecord(B.ev0, s);
