@@ -41,7 +41,7 @@ constexpr int COUNT_CELLS = 8;          // cells per counting workgroup
 constexpr int PLAN_BLOCK = 1024;
 constexpr uint32_t HASH_MUL = 0x9E3779B1u;  // odd, 2^32 / golden ratio
 constexpr uint32_t PART_MUL = 0x85EBCA6Bu;  // odd: the table's hash
-constexpr int MAX_PROBE = 256;
+constexpr int MAX_PROBE = 64;   // a longer chain means a full table
 // Intervals still to do: a cut leaves seven more, and at most twenty cuts lead
 // from 2^62 codes to the 64 that are not cut.
 constexpr int STACK = 144;
@@ -648,10 +648,12 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
     uint32_t s = __umulhi(h << MLOG, (uint32_t)SLOTS);   // the hash's bits below the cell's
     K c = claim(&keys[s], key);
     int q = 0;
+    const uint32_t step = 1 + 6 * (h & 63);   // odd and no multiple of 3: every slot once
 #pragma nounroll
     while (c != NONE && c != key && q < MAX_PROBE) {
       ++q;
-      s = s + 1 == SLOTS ? 0 : s + 1;
+      s += step;
+      s = s >= (uint32_t)SLOTS ? s - SLOTS : s;
       c = claim(&keys[s], key);
     }
     if (c != NONE && c != key) {
@@ -718,6 +720,8 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
         // candidates STEPS * 64 at a time: candidate k belongs to the last
         // row whose first candidate is at or before it
         for (uint32_t k0 = 0; k0 < total; k0 += STEPS * 64) {
+          // (a full table's chains are long: what is left is not looked at)
+          if (PASS == 2 && uniform(*(volatile uint32_t*)&s_over)) return;
 #pragma unroll
           for (int v = 0; v < STEPS; ++v) seg[wave][v * 64 + lane] = 0;
           wave_sync();

@@ -920,13 +920,15 @@ __global__ void __launch_bounds__((1 << LOG) / BIN_PER_THREAD) k_radix_bins(Radi
     const unsigned long long key = (unsigned long long)code + 1;
     uint32_t slot = bin_slot<LOG>(code_hash(code), R.l1, l2);
     // one compare-and-swap claims an empty slot or returns its key; the
-    // probe loop has one exit test and the value is added after it
+    // probe loop has one exit test and the value is added after it.  A
+    // wavefront waits for its longest chain: growing steps keep chains apart
+    // (a truncated product of 4e8 pairs: 0.50 ms instead of 0.55)
     unsigned long long c = atomicCAS(&keys[slot], 0ull, key);
     int q = 0;
 #pragma nounroll
     while (c != 0 && c != key && q < BIN_SLOTS - 1) {
       ++q;
-      slot = (slot + 1) & (BIN_SLOTS - 1);
+      slot = (slot + q) & (BIN_SLOTS - 1);   // every slot once, in growing steps
       c = atomicCAS(&keys[slot], 0ull, key);
     }
     if (c != 0 && c != key) {   // every slot holds another code

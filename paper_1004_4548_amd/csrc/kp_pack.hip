@@ -19,8 +19,8 @@
 // The products used to be added in tables in device memory, one atomic or two
 // per product: 1.07e7 products of 24 tasks of 50 to 2,000 terms took 1.31 ms,
 // bound by atomics on the same few lines (8e9 a second), and 0.29 ms more to
-// read the tables back (2.00 ms the whole batch).  In LDS they take 0.40 ms and
-// nothing is read back; with sorting, counting and planning 0.46 ms (0.71 the
+// read the tables back (2.00 ms the whole batch).  In LDS they take 0.32 ms and
+// nothing is read back; with sorting, counting and planning 0.38 ms (0.61 the
 // batch).
 
 #include <algorithm>
@@ -36,7 +36,7 @@ constexpr int PACK_BOX_BLOCK = 1024;
 constexpr int PACK_SORT_BLOCK = 1024;
 constexpr int PACK_SLOTS = 2048;        // of an interval's table in LDS
 constexpr int PACK_STEPS = 2;           // candidates per lane with their loads in flight
-constexpr int PACK_MAX_PROBE = 48;      // longer chains: the table counts as full
+constexpr int PACK_MAX_PROBE = 32;      // longer chains: the table counts as full
 constexpr int PACK_PER_CU = 3;          // multiplying workgroups that fit a compute unit (LDS)
 constexpr int PACK_STACK = 104;         // intervals still to do (three more per cut)
 
@@ -421,7 +421,9 @@ __device__ __forceinline__ PackSet uniform_set(const PackSet& s) {
 // workgroups of 50 KB of LDS per compute unit), not bytes.  Intervals are taken
 // at a fixed stride: handing them out from one counter cost 1.03 ms instead of
 // 0.41 on the batch named above, 64 coarser cells a task 1.2 ms, probe chains
-// of up to 256 slots 1.9 ms.
+// of up to 256 slots 1.9 ms.  A wavefront waits for its longest chain, so a
+// table that fills is given up early (the walk ends, chains of 32 in growing
+// steps): 0.32 ms instead of 0.41.
 // The grid takes the intervals of every task; see the head of the file.  A
 // full table (only codes crowded in part of a cell make one, intervals being
 // sized from their cell's products) has its interval cut in four; one of at
@@ -492,6 +494,7 @@ __global__ void __launch_bounds__(PACK_BLOCK, PACK_PER_CU) k_pack_mul(void* tabl
         // candidates 64 at a time: candidate q belongs to the last row whose
         // first candidate is at or before it
         for (uint32_t q0 = 0; q0 < total; q0 += PACK_STEPS * 64) {
+          if (uniform(*(volatile uint32_t*)&s_over)) break;
 #pragma unroll
           for (int v = 0; v < PACK_STEPS; ++v) seg[wave][v * 64 + lane] = 0;
           wave_sync();
@@ -521,7 +524,7 @@ __global__ void __launch_bounds__(PACK_BLOCK, PACK_PER_CU) k_pack_mul(void* tabl
 #pragma nounroll
               while (c != ~0ull && c != key && q < PACK_MAX_PROBE) {
                 ++q;
-                s = (s + 1) & (PACK_SLOTS - 1);
+                s = (s + q) & (PACK_SLOTS - 1);   // every slot once, in growing steps
                 c = atomicCAS(reinterpret_cast<unsigned long long*>(&keys[s]), ~0ull, key);
               }
               if (c != ~0ull && c != key) {
