@@ -108,13 +108,15 @@ def batch_bytes(staged, plans):
 
 
 def pack_bytes(s):
-    """A bound on the device bytes of one product in a pack: its result
-    (at most one term per pair: exponents and coefficient), codes and
-    accumulator (at most 8 words per result term: a hash table of up to four
-    times the bound, two words a slot, or one word per code up to twice that
-    many slots)."""
+    """A bound on the device bytes of one product in a pack: its result (at
+    most one term per pair: exponents and coefficient) and its part of the
+    arena (the sorted factors with their bucket starts, cells and intervals of
+    codes: a fixed part, 40 bytes a term and a fraction of a byte per pair;
+    64 bytes per pair are held as before where that is more)."""
     na, nb = s.a.coef.shape[0], s.b.coef.shape[0]
-    return _align(s.pairs * (4 * s.a.nv + 8 + 64)) + _align(8 * (na + nb)) + 4096
+    arena = max(64 * s.pairs + _align(8 * (na + nb)) + 4096,
+                s.pairs // 4 + _align(40 * (na + nb)) + 24576)
+    return _align(s.pairs * (4 * s.a.nv + 8)) + _align(arena) + 512
 
 
 class SlotMemory:

@@ -62,3 +62,17 @@ def test_matches_oracle(graph):
                 assert_tolerance([ge], gc, [oe], oc, oab, TOL, what)
             else:
                 assert_exact([ge], gc, [oe], oc, what)
+
+
+@pytest.mark.parametrize("na,nb", [(1, 1), (2, 3), (60, 70), (1, 4000), (300, 2000)])
+def test_serving_bound_covers_the_arena(na, nb):
+    """The bytes that a server sets aside for products of a pack hold their
+    results and the pack's arena."""
+    from types import SimpleNamespace
+    from paper_1004_4548_amd import serve
+    rng = np.random.default_rng([na, nb])
+    (ea, ca), (eb, cb) = _factor(rng, na, 4, 500, False), _factor(rng, nb, 4, 500, False)
+    prods = [(kp.Poly(dev(ea), dev(ca)), kp.Poly(dev(eb), dev(cb))) for _ in range(7)]
+    _, nbytes = kp.Pack(8).plan(prods)
+    s = SimpleNamespace(a=prods[0][0], b=prods[0][1], pairs=na * nb)
+    assert nbytes <= 7 * serve.pack_bytes(s)
