@@ -655,6 +655,7 @@ constexpr int64_t DIRECT_ROWS = 24000;
 // against 0.27.
 constexpr int64_t DIRECT_SMALL_ROWS = 2048;
 constexpr int64_t DIRECT_PLACE = 4096;  // larger sets are placed by a launch of their own
+constexpr int64_t DIRECT_LOPSIDED = 50;   // columns per row
 // Columns at most: crowded ones are sorted by counting within their bucket,
 // 3.5 ms for this many in one bucket.
 constexpr int64_t DIRECT_COLUMNS = 1 << 18;
