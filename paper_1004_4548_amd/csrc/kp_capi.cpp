@@ -1316,7 +1316,8 @@ namespace {
 // context's timing events around the accumulation kernel when enabled.
 // Options of the from-exponents path: the multiply writes decoded exponents
 // into `exps` (dense: its output copy; partitioned hash: its bins), and the
-// dense output scan posts the count to the mailbox under `seq` (0: no post).
+// kernel that ends the call posts the count to the mailbox under `seq` (0: no
+// post).
 // `decoded` and `posted` report which were taken.
 struct ExpsOut {
   int32_t* exps;
@@ -1570,7 +1571,12 @@ kp_status enqueue_laurent(kp_ctx* ctx, const kp_layout* layout, kp_dtype dtype, 
       }
       if (e == hipSuccess) e = launch_hash_compact(H, dtype, stream);
     }
-    if (e == hipSuccess) e = launch_finalize(h.meta, out_cap, out_n, &ctx->status->err, stream);
+    // posted here when no decode follows
+    const bool post = xo && xo->decoded && xo->seq;
+    if (post) xo->posted = true;
+    if (e == hipSuccess)
+      e = launch_finalize(h.meta, out_cap, out_n, &ctx->status->err, stream,
+                          post ? xo->mb : nullptr, post ? xo->seq : 0);
   }
   if (e != hipSuccess) return hip_fail(ctx, e, "kp_mul_laurent launch");
   return KP_OK;
@@ -1583,7 +1589,10 @@ struct PoissonOut {
   int32_t* y;
   uint8_t* sin;
   DevLayout dec;
+  Mailbox* mb;     // as in ExpsOut
+  uint64_t seq;
   bool decoded;
+  bool posted;
 };
 
 kp_status enqueue_poisson(kp_ctx* ctx, const kp_layout* layout, kp_mode mode,
@@ -1676,7 +1685,11 @@ kp_status enqueue_poisson(kp_ctx* ctx, const kp_layout* layout, kp_mode mode,
                               stream);
     if (e == hipSuccess) e = launch_hash_compact(H, KP_F64, stream);
   }
-  if (e == hipSuccess) e = launch_finalize(h.meta, out_cap, out_n, &ctx->status->err, stream);
+  const bool post = po && po->decoded && po->seq;
+  if (post) po->posted = true;
+  if (e == hipSuccess)
+    e = launch_finalize(h.meta, out_cap, out_n, &ctx->status->err, stream,
+                        post ? po->mb : nullptr, post ? po->seq : 0);
   if (e != hipSuccess) return hip_fail(ctx, e, "kp_mul_poisson launch");
   return KP_OK;
 }
@@ -1929,7 +1942,9 @@ kp_status kp_mul_poisson_exps(kp_ctx* ctx, const kp_layout* layout, kp_mode mode
     e = launch_encode2(make_dev_layout(*layout, 0), make_dev_layout(*layout, 1), na, nb, a_x, a_y,
                        a_sin, kxa, kya, b_x, b_y, b_sin, kxb, kyb, &ctx->status->err, stream);
   if (e != hipSuccess) return hip_fail(ctx, e, "kp_mul_poisson_exps encode");
-  PoissonOut po{out_x, out_y, out_sin, make_dev_layout(*layout, 0), false};
+  const bool sync = !(flags & KP_FLAG_ASYNC);
+  PoissonOut po{out_x, out_y, out_sin, make_dev_layout(*layout, 0), ctx->mb_dev,
+                sync ? next_seq(ctx) : 0, false, false};
   st = enqueue_poisson(ctx, layout, mode, kxa, kya, a_sin, a_coef, na, kxb, kyb, b_sin, b_coef,
                        nb, ok, out_coef, ncodes, out_n, static_cast<char*>(workspace) + c.off,
                        workspace_bytes - c.off, stream, true, &po);
@@ -1939,8 +1954,8 @@ kp_status kp_mul_poisson_exps(kp_ctx* ctx, const kp_layout* layout, kp_mode mode
                         &ctx->status->err, stream);
     if (e != hipSuccess) return hip_fail(ctx, e, "kp_mul_poisson_exps decode");
   }
-  if (flags & KP_FLAG_ASYNC) return finish(ctx, flags, stream, "kp_mul_poisson_exps");
-  return wait_count(ctx, out_n, n_host, stream, "kp_mul_poisson_exps");
+  if (!sync) return finish(ctx, flags, stream, "kp_mul_poisson_exps");
+  return wait_count(ctx, out_n, n_host, stream, "kp_mul_poisson_exps", po.posted ? po.seq : 0);
 }
 
 // ------------------------------------------------------------ batches

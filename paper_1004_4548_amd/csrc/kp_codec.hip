@@ -394,7 +394,11 @@ __global__ void __launch_bounds__(256) k_zero(uint4* p, size_t n16, uint8_t* tai
   if (blockIdx.x == 0 && threadIdx.x < ntail) tail[threadIdx.x] = 0;
 }
 
-__global__ void k_finalize(const Meta* m, int64_t out_cap, int64_t* out_n, uint32_t* ctx_err) {
+// The call's end: the count (or -status) and the latched errors, posted to the
+// mailbox too when the host waits for them and nothing follows (a launch of
+// its own for the post costs about 10 us of a waited call).
+__global__ void k_finalize(const Meta* m, int64_t out_cap, int64_t* out_n, uint32_t* ctx_err,
+                           Mailbox* mb, uint64_t seq) {
   if (threadIdx.x != 0) return;
   // errors of this call, and any latched on the context by an earlier
   // asynchronous call (an encode that found an exponent out of range)
@@ -403,10 +407,10 @@ __global__ void k_finalize(const Meta* m, int64_t out_cap, int64_t* out_n, uint3
   if (cnt > out_cap) e |= ERR_CAPACITY;
   if (e) {
     atomicOr(ctx_err, e);
-    *out_n = -(int64_t)first_error(e);
-  } else {
-    *out_n = cnt;
+    cnt = -(int64_t)first_error(e);
   }
+  *out_n = cnt;
+  if (mb) post_count(mb, seq, cnt, e);
 }
 
 // Range flags of int64 coefficients: bit0 all fit int32, bit1 all fit in a
@@ -528,8 +532,8 @@ hipError_t launch_zero(void* p, size_t bytes, hipStream_t s) {
 }
 
 hipError_t launch_finalize(const Meta* m, int64_t out_cap, int64_t* out_n, uint32_t* ctx_err,
-                           hipStream_t s) {
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(64), 0, s, m, out_cap, out_n, ctx_err);
+                           hipStream_t s, Mailbox* mb, uint64_t seq) {
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(64), 0, s, m, out_cap, out_n, ctx_err, mb, seq);
   return hipGetLastError();
 }
 

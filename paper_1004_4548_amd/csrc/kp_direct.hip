@@ -1003,23 +1003,6 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
   }
 }
 
-// The call's end: the count (or -status) and the context's latched errors as
-// k_finalize, posted to the mailbox too when the host waits for them.
-__global__ void k_rd_finish(const Meta* m, int64_t out_cap, int64_t* out_n, uint32_t* ctx_err,
-                            Mailbox* mb, uint64_t seq) {
-  if (threadIdx.x != 0) return;
-  uint32_t e = m->err | *ctx_err;
-  const int64_t cnt = m->out_count;
-  if (cnt > out_cap) e |= ERR_CAPACITY;
-  int64_t n = cnt;
-  if (e) {
-    atomicOr(ctx_err, e);
-    n = -(int64_t)first_error(e);
-  }
-  *out_n = n;
-  if (mb) post_count(mb, seq, n, e);
-}
-
 template <typename T, typename K, int NT, int MLOG, int SLOTS>
 void launch_mul(const DirectArgs& R, hipStream_t s) {
   hipLaunchKernelGGL((k_rd_mul<T, K, NT, MLOG, SLOTS>), dim3((unsigned)R.grid), dim3(NT), 0, s,
@@ -1078,9 +1061,7 @@ hipError_t launch_direct(const DirectArgs& R, kp_dtype dt, int64_t* out_n, uint3
   else if (dt == KP_I128) launch_mul_typed<I128, 2048, 512, 2048>(R, s);
   else launch_mul_typed<int64_t, 4096, 1024, 3072>(R, s);
   if (R.ev1) (void)hipEventRecord(R.ev1, s);
-  hipLaunchKernelGGL(k_rd_finish, dim3(1), dim3(64), 0, s, R.meta, R.out_cap, out_n, ctx_err, mb,
-                     seq);
-  return hipGetLastError();
+  return launch_finalize(R.meta, R.out_cap, out_n, ctx_err, s, mb, seq);
 }
 
 }  // namespace kp

@@ -401,8 +401,9 @@ hipError_t launch_decode(const DevLayout& L, int poisson, int64_t n, const int64
 // misc
 hipError_t launch_meta_init(Meta* m, hipStream_t s);
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
+// mb: the count is posted there under seq (null: not).
 hipError_t launch_finalize(const Meta* m, int64_t out_cap, int64_t* out_n, uint32_t* ctx_err,
-                           hipStream_t s);
+                           hipStream_t s, Mailbox* mb = nullptr, uint64_t seq = 0);
 hipError_t launch_coef_range(const int64_t* a, int64_t na, const int64_t* b, int64_t nb, Meta* m,
                              hipStream_t s);
 
@@ -701,9 +702,8 @@ struct DirectArgs {
   hipEvent_t ev0, ev1;
 };
 hipError_t direct_setup();
-// mb: the count is posted there under seq (null: not).
 hipError_t launch_direct(const DirectArgs& R, kp_dtype dt, int64_t* out_n, uint32_t* ctx_err,
-                         Mailbox* mb, uint64_t seq, hipStream_t s);
+                         Mailbox* mb, uint64_t seq, hipStream_t s);   // mb, seq: launch_finalize
 
 // Columns are crowded when a term shares its bucket with more than this many
 // on average, or with this many times a bucket's even share.  Random sparse
