@@ -138,7 +138,11 @@ typedef struct kp_tune {
                                through HBM, each group accumulated in an LDS table
                                (workspace 34 bytes per product); 0 = one open-addressing
                                table in HBM; 1 (default) = grouped when the products are
-                               at most 4 times the result bound, else the table          */
+                               at most 4 times the result bound, else the table; sparse
+                               Laurent products then need no grouping when the smaller
+                               factor has at most 24,000 terms and the other hash_* and
+                               grouping knobs are at their defaults: each interval's
+                               products are found from the sorted factors (same workspace) */
   int32_t hash_bucket;      /* hash, Laurent, int64/fp64: > 0 selects Section 3.2's bucketed
                                table instead of the above, with this many slots per bucket
                                (1 .. 16): product code e goes to bucket e mod N, where it is
@@ -161,8 +165,8 @@ typedef struct kp_tune {
                                product is written once, to a hash bin of its range);
                                1 = two levels of hash bits through HBM (always used for
                                Poisson series and 128-bit sums); 0 (default) = by range
-                               for products spread thinly over the code space (at most one
-                               per 64 codes), else, and under a truncation (the two-level
+                               (or ungrouped, see hash_partitioned) for products spread
+                               thinly over the code space (at most one per 64 codes), else, and under a truncation (the two-level
                                grouping drops pairs over the limit before forming them),
                                two levels.  Either
                                way a bin whose distinct codes overflow its table is redone
@@ -230,7 +234,7 @@ kp_status kp_ctx_set_harmonic_truncation(kp_ctx* ctx, int32_t ny, const int32_t*
                                          int64_t max_order);
 kp_status kp_ctx_clear_truncation(kp_ctx* ctx);
 
-/* Hash-table statistics (Section 3.2: open addressing with linear probing).
+/* Hash-table statistics (Section 3.2: open addressing).
    While enabled, every hash-mode multiply adds to two device counters in the
    context's status block: the number of term products inserted (nonzero
    ones) and the number of slots visited beyond each product's home slot.
