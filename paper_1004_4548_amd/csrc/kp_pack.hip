@@ -197,17 +197,33 @@ __global__ void __launch_bounds__(PACK_SORT_BLOCK) k_pack_sort(void* table) {
     }
     if (crowd) {   // the same for every thread
       __syncthreads();
-      for (int64_t t = tid; t < S.n; t += PACK_SORT_BLOCK) {
-        const int64_t k = T.tmp_k[t], b = k >> S.shift;
-        const int e = b + 1 < S.nbk ? hist[b + 1] : (int)S.n;
-        int at = hist[b];
-#pragma unroll 4
-        for (int o = hist[b]; o < e; ++o) {
-          const int64_t y = T.tmp_k[o];
-          at += y < k || (y == k && o < t) ? 1 : 0;
+      // merge sort: a term's place in two merged runs is its own index plus the
+      // terms of the other run before it (the ranks are no longer needed)
+      int64_t *src = T.tmp_k, *dst = S.k;
+      int32_t *si = T.tmp_i, *di = S.rank;
+      for (int64_t run = 1; run < S.n; run *= 2) {
+        for (int64_t t = tid; t < S.n; t += PACK_SORT_BLOCK) {
+          const int64_t k = src[t], first = t / (2 * run) * (2 * run);
+          const bool left = t < first + run;
+          const int64_t o0 = left ? min(S.n, first + run) : first;
+          const int64_t o1 = left ? min(S.n, first + 2 * run) : first + run;
+          // (equal codes: the left run's terms first)
+          const int64_t o = first_from(src, (uint32_t)o0, (uint32_t)o1, left ? k : k + 1);
+          const int64_t at = first + (t - (left ? first : first + run)) + (o - o0);
+          dst[at] = k;
+          di[at] = si[t];
         }
-        S.k[at] = k;
-        S.c[at] = c[T.tmp_i[t]];
+        __syncthreads();
+        int64_t* const k0 = src;
+        src = dst;
+        dst = k0;
+        int32_t* const i0 = si;
+        si = di;
+        di = i0;
+      }
+      for (int64_t t = tid; t < S.n; t += PACK_SORT_BLOCK) {
+        S.c[t] = c[si[t]];
+        if (src != S.k) S.k[t] = src[t];
       }
       __syncthreads();   // hist has been read
       const PackSet& A = T.set[0];
