@@ -29,6 +29,7 @@
 #include <climits>
 #include <type_traits>
 
+#include "kp_cut.h"
 #include "kp_internal.h"
 
 namespace kp {
@@ -42,9 +43,6 @@ constexpr int PLAN_BLOCK = 1024;
 constexpr uint32_t HASH_MUL = 0x9E3779B1u;  // odd, 2^32 / golden ratio
 constexpr uint32_t PART_MUL = 0x85EBCA6Bu;  // odd: the table's hash
 constexpr int MAX_PROBE = 64;   // a longer chain means a full table
-// Intervals still to do: a cut leaves seven more, and at most twenty cuts lead
-// from 2^62 codes to the 64 that are not cut.
-constexpr int STACK = 144;
 constexpr int PARTS = 72;   // stretches still to do, one more per halving
 constexpr int ROWS = 1;     // rows per lane and batch
 constexpr int STEPS = 2;    // candidates per lane with their loads in flight
@@ -525,7 +523,7 @@ __device__ __forceinline__ void each_digit(const DirectArgs& R, const UnitDigits
 //   2. When more products share cells than the table takes, they are added one
 //      stretch of codes at a time, halving a stretch that still overflows.
 // An interval of far more products than planned (codes that crowd in a small
-// part of a cell) is cut into eight before anything is written.
+// part of a cell) is cut into pieces before anything is written.
 //
 // What bounds it: VALU issue and the latency of the chain row -> columns ->
 // cell -> result slot, not bytes.  Of 1.66 ms on 7,919 x 12,347 terms (9.8e7
@@ -545,6 +543,7 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
   // products of an interval that is cut; fewer when its codes crowd, since
   // those that share cells must then fit the table
   constexpr uint32_t CROWD = (1u << MLOG) / 4, CROWD_FEW = (1u << MLOG) / 9;
+  constexpr K UNCUT = (K)1 << DIRECT_DONE_LOG;   // codes of an interval that is never cut
   static_assert(SLOTS % NT == 0, "each wavefront owns a stretch of the table");
   static_assert(WORDS % NT == 0, "each thread owns words of the marks");
   __shared__ uint32_t marked[WORDS], shared[WORDS];
@@ -559,9 +558,10 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
   __shared__ int64_t s_base;
   __shared__ uint32_t s_cursor, s_products, s_over;
   __shared__ uint32_t s_next;             // rows handed out
-  __shared__ int64_t s_lo[STACK];         // intervals still to do
-  __shared__ K s_width[STACK];
-  __shared__ K s_sample[64];              // offsets of products, when the columns are crowded
+  __shared__ int64_t s_lo[DIRECT_STACK];  // intervals still to do
+  __shared__ K s_width[DIRECT_STACK];
+  __shared__ K s_sample[CUT_SAMPLES];     // offsets of products, when the columns are crowded
+  __shared__ int s_pieces;                // of a cut
   __shared__ K p_lo[PARTS], p_hi[PARTS];   // stretches of the shared products
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t units = uniform(R.meta->nbins);
@@ -690,7 +690,7 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
         if (lane == 0) bt = atomicAdd(&s_next, (uint32_t)(ROWS * 64));
         const uint32_t ib = i0 + lane_value(bt, 0);
         if (ib >= i1) break;
-        if (PASS == 0 && *(volatile uint32_t*)&s_products > MOST && width > 64) return;
+        if (PASS == 0 && *(volatile uint32_t*)&s_products > MOST && width > UNCUT) return;
         if (PASS == 2 && *(volatile uint32_t*)&s_over) return;
         int64_t a[ROWS];
         uint32_t cnt[ROWS], excl[ROWS];
@@ -772,8 +772,14 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
             if (PASS == 0) {
               const uint64_t oks = __ballot(ok);
               products += (uint32_t)__popcll(oks);
-              if (CROWDS && oks && lane == (int)__builtin_ctzll(oks))
-                s_sample[(wave + NW * (products >> 6)) & 63] = key;
+              if (CROWDS && oks) {
+                // a sample per step, from a lane that changes: a step that
+                // begins with a row begins with the row's least code
+                const uint32_t z = ((products + wave) * HASH_MUL) >> 26;
+                const uint64_t turned = (oks >> z) | (oks << ((64 - z) & 63));
+                if (lane == (((int)__builtin_ctzll(turned) + (int)z) & 63))
+                  s_sample[(wave + NW * (products >> 6)) & (CUT_SAMPLES - 1)] = key;
+              }
               if (ok && (atomicOr(&marked[cell >> 5], bit) & bit)) atomicOr(&shared[cell >> 5], bit);
               continue;
             }
@@ -907,35 +913,34 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
     clear_table();
     if (tid == 0) s_next = 0;
     if (tid == 0) s_cursor = s_products = 0;
-    if (tid < 64) s_sample[tid] = NONE;
+    if (tid < CUT_SAMPLES) s_sample[tid] = NONE;
     __syncthreads();
     walk(std::integral_constant<int, 0>{}, 0, width, false);
     __syncthreads();
     const uint32_t products = uniform(s_products);
-    if (products > most && width > 64) {   // the same for every thread
+    if (products > most && width > UNCUT) {   // the same for every thread
       if (wave == 0) {
-        // into equal parts, or at the octiles of sampled products: codes that
-        // crowd on several scales would take a cut per scale
         const K key = s_sample[lane];
         int rank = 0;
 #pragma unroll 8
-        for (int o = 0; o < 64; ++o) {
+        for (int o = 0; o < CUT_SAMPLES; ++o) {
           const K y = s_sample[o];
           rank += y < key || (y == key && o < lane) ? 1 : 0;
         }
-        const int n = (int)__popcll(__ballot(key != NONE));
-        const bool few = n < 32;
-        const K step = width / 8;   // (width > 64)
-        const int piece = few ? lane : rank / (n / 8);
-        if (lane == 0) s_lo[sp] = lo;
-        if (few ? lane > 0 && lane < 8 : key != NONE && rank > 0 && rank % (n / 8) == 0 && piece < 8)
-          s_lo[sp + piece] = lo + (int64_t)(few ? step * (K)lane : key);
+        const int n = (int)__popcll(__ballot(key != NONE));   // (NONE is the greatest)
+        wave_sync();
+        s_sample[rank] = key;
+        wave_sync();
+        // (the same in every lane)
+        const int m = cut_points<K>([&](int i) { return uniform(s_sample[i]); }, n, width, sp,
+                                    DIRECT_STACK, DIRECT_DONE_LOG, [&](int p, K x, K y) {
+                                      s_lo[sp + p] = lo + (int64_t)x;
+                                      s_width[sp + p] = y - x;
+                                    });
+        if (lane == 0) s_pieces = m;
       }
       __syncthreads();
-      if (tid < 8)
-        s_width[sp + tid] = (K)((tid < 7 ? s_lo[sp + tid + 1] : lo + (int64_t)width) - s_lo[sp + tid]);
-      sp += 8;
-      __syncthreads();
+      sp += (int)uniform((uint32_t)s_pieces);
       continue;
     }
     // products alone in their cells: cells marked but not shared
