@@ -26,6 +26,7 @@
 #include <algorithm>
 #include <climits>
 
+#include "kp_cut.h"
 #include "kp_internal.h"
 
 namespace kp {
@@ -38,7 +39,7 @@ constexpr int PACK_SLOTS = 2048;        // of an interval's table in LDS
 constexpr int PACK_STEPS = 2;           // candidates per lane with their loads in flight
 constexpr int PACK_MAX_PROBE = 32;      // longer chains: the table counts as full
 constexpr int PACK_PER_CU = 3;          // multiplying workgroups that fit a compute unit (LDS)
-constexpr int PACK_STACK = 104;         // intervals still to do (three more per cut)
+static_assert(PACK_SLOTS == 1 << PACK_DONE_LOG, "an interval the table indexes is not cut");
 
 struct PackView {
   PackHeader* h;
@@ -442,8 +443,10 @@ __device__ __forceinline__ PackSet uniform_set(const PackSet& s) {
 // steps): 0.32 ms instead of 0.41.
 // The grid takes the intervals of every task; see the head of the file.  A
 // full table (only codes crowded in part of a cell make one, intervals being
-// sized from their cell's products) has its interval cut in four; one of at
-// most PACK_SLOTS codes is indexed directly and always fits.
+// sized from their cell's products) has its interval cut at keys that it holds;
+// one of at most PACK_SLOTS codes is indexed directly and always fits.  Those
+// keys are of the rows walked so far, the least ones: a piece may hold nearly
+// all that is left, which is why the cut's own bounds (kp_cut.h) keep the stack.
 __global__ void __launch_bounds__(PACK_BLOCK, PACK_PER_CU) k_pack_mul(void* table) {
   constexpr int NW = PACK_BLOCK / 64, PER = PACK_SLOTS / PACK_BLOCK;
   __shared__ uint64_t keys[PACK_SLOTS], vals[PACK_SLOTS];
@@ -454,6 +457,7 @@ __global__ void __launch_bounds__(PACK_BLOCK, PACK_PER_CU) k_pack_mul(void* tabl
   __shared__ int64_t s_base, s_lo[PACK_STACK];
   __shared__ PackDigit s_dig[KP_MAX_VARS];   // the task's decode
   __shared__ uint64_t s_width[PACK_STACK];
+  __shared__ int s_pieces;                   // of a cut
   const PackView P = view(table);
   const unsigned long long units = P.h->nunits;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -556,28 +560,28 @@ __global__ void __launch_bounds__(PACK_BLOCK, PACK_PER_CU) k_pack_mul(void* tabl
       if (s_over) {   // the same for every thread
         __syncthreads();
         if (wave == 0) {
-          // cut at the quartiles of 64 of the table's keys
-          const uint64_t key = keys[lane * (PACK_SLOTS / 64)];
+          const uint64_t key = keys[lane * (PACK_SLOTS / CUT_SAMPLES)];
           int rank = 0;
 #pragma unroll 8
-          for (int o = 0; o < 64; ++o) {
-            const uint64_t y = keys[o * (PACK_SLOTS / 64)];
+          for (int o = 0; o < CUT_SAMPLES; ++o) {
+            const uint64_t y = keys[o * (PACK_SLOTS / CUT_SAMPLES)];
             rank += y < key || (y == key && o < lane) ? 1 : 0;
           }
-          const int n = (int)__popcll(__ballot(key != ~0ull));
-          const bool few = n < 8;   // (then equally wide)
-          const uint64_t step = width / 4;
-          if (lane == 0) s_lo[sp] = lo;
-          if (few ? lane > 0 && lane < 4 : key != ~0ull && rank > 0 && rank % (n / 4) == 0 && rank / (n / 4) < 4) {
-            const int piece = few ? lane : rank / (n / 4);
-            s_lo[sp + piece] = lo + (int64_t)(few ? step * lane : key);
-          }
+          const int n = (int)__popcll(__ballot(key != ~0ull));   // (empty slots are the greatest)
+          uint64_t* sorted = row_off[0];   // (no row is being walked)
+          sorted[rank] = key;
+          wave_sync();
+          // (the same in every lane)
+          const int m = cut_points<uint64_t>([&](int i) { return uniform(sorted[i]); }, n, width,
+                                             sp, PACK_STACK, PACK_DONE_LOG,
+                                             [&](int p, uint64_t x, uint64_t y) {
+                                               s_lo[sp + p] = lo + (int64_t)x;
+                                               s_width[sp + p] = y - x;
+                                             });
+          if (lane == 0) s_pieces = m;
         }
         __syncthreads();
-        if (tid < 4)
-          s_width[sp + tid] = (uint64_t)((tid < 3 ? s_lo[sp + tid + 1] : hi + 1) - s_lo[sp + tid]);
-        sp += 4;
-        __syncthreads();
+        sp += (int)uniform((uint32_t)s_pieces);
         continue;
       }
       // nonzero sums (for fp64 both signed zeros are dropped) to the front of
