@@ -307,7 +307,7 @@ struct Plan {
   // 2^dcw codes, products per interval, intervals, buckets of rows and columns
   bool direct = false, dswap = false, dsmall = false, dwide = false;
   int dcw = 0, dshift[2] = {0, 0};
-  int64_t dncell = 0, dtarget = 1, dunits = 0, dgrid = 0, dncrowd = 0;
+  int64_t dncell = 0, dtarget = 1, dunits = 0, dgrid = 0, dncrowd = 0, dpeak = 0;
   int64_t dmax[2] = {0, 0}, dnbk[2] = {0, 0};
 };
 
@@ -587,6 +587,11 @@ bool direct_shape(const kp_ctx* ctx, const kp_layout* L, int64_t na, int64_t nb,
   const int64_t wgs = (p->dsmall ? 4 : 1) * (int64_t)ctx->num_cu;
   p->dtarget = std::min(full, std::max<int64_t>(256, pairs / (2 * wgs)));
   p->dgrid = p->dncell + (pairs + pairs / 2) / p->dtarget + 64;
+  // One bucket of columns may give an interval its terms times the rows.  That
+  // does little harm below two intervals' products or a compute unit's share;
+  // above, products are sampled to see whether they crowd (a sample of 8,192
+  // takes 90 us; random terms, some ten to the fullest bucket, do without).
+  p->dpeak = std::max(2 * full, pairs / ctx->num_cu);
   // crowded columns: sampled cells of up to a quarter of an interval, which 32-bit offsets
   // may cut once more per 2^31 codes (at most once per cell of equal width)
   p->dncrowd = 64;
@@ -632,6 +637,10 @@ DirectArgs direct_args(const Plan& p, kp_dtype dt, const kp_layout* L, const Dir
   R.wide_codes = p.dwide ? 1 : 0;
   R.max_units = p.dunits;
   R.grid = p.dgrid;
+  R.peak = p.dpeak;
+  const double share = (double)p.dtarget * (double)p.dncrowd / ((double)na * (double)nb);
+  R.near = std::ldexp(share, p.dcw);
+  R.nnear = (int32_t)std::max((double)DIRECT_NEAR, std::min(1e6, std::ceil(8.0 * share)));
   R.ncrowd = (int32_t)p.dncrowd;
   R.bounds = d.bounds;
   R.tmp_k = d.tmp_k;

@@ -12,10 +12,10 @@
 //
 // Intervals: the code space is cut into cells of 2^cw codes; a counting pass
 // bounds the products of every cell, and a cell is cut into equal intervals of
-// about `target` products.  Crowded columns (a box that an outlier makes huge)
-// are sorted within their buckets too, so that a row finds exactly the columns
-// of an interval, and the cells are then bounded by a sorted sample of the
-// products: 600 x 900 terms of three variables in [0, 24) and one outlier
+// about `target` products.  Crowded columns (a box that an outlier makes huge),
+// and columns whose products crowd because the rows do, are sorted within their
+// buckets too, so that a row finds exactly the columns of an interval, and the
+// cells are then bounded by a sorted sample of the products: 600 x 900 terms of three variables in [0, 24) and one outlier
 // each would otherwise be one workgroup's, 95 ms instead of 0.34 (0.50 through
 // the groups); 5,000 x 6,000 terms of five variables take 3.6 ms (139 through
 // the groups).
@@ -124,7 +124,11 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_rd_sort(DirectArgs R) {
   extern __shared__ __align__(8) int32_t hist[];
   __shared__ uint32_t s_ws[SORT_BLOCK / 64 + 1];
   __shared__ unsigned long long s_sq;
-  if (threadIdx.x == 0) s_sq = 0;
+  __shared__ uint32_t s_most;   // terms of the fullest bucket
+  if (threadIdx.x == 0) {
+    s_sq = 0;
+    s_most = 0;
+  }
   const DirectSet& S = R.set[blockIdx.x];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   for (int64_t k = tid; k < S.nbk; k += SORT_BLOCK) hist[k] = 0;
@@ -145,15 +149,19 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_rd_sort(DirectArgs R) {
   // exclusive scan: each wavefront a contiguous stretch of buckets, 64 at a time
   const int64_t per = ((S.nbk + SORT_BLOCK - 1) / SORT_BLOCK) * 64;
   const int64_t b0 = min(S.nbk, wave * per), b1 = min(S.nbk, b0 + per);
-  uint32_t sum = 0;
+  uint32_t sum = 0, most = 0;
   uint64_t sq = 0;
   for (int64_t b = b0; b < b1; b += 64) {
     const uint32_t v = b + lane < b1 ? (uint32_t)hist[b + lane] : 0u;
     sum += lane_value(wave_scan_add(v), 63);
+    most = max(most, v);
     sq += (uint64_t)v * v;
   }
   if (lane == 0) s_ws[wave] = sum;
-  if (blockIdx.x == 1 && sq) atomicAdd(&s_sq, (unsigned long long)sq);
+  if (blockIdx.x == 1 && sq) {
+    atomicAdd(&s_sq, (unsigned long long)sq);
+    atomicMax(&s_most, most);
+  }
   __syncthreads();
   uint32_t run = 0;
   for (int w = 0; w < wave; ++w) run += s_ws[w];
@@ -177,42 +185,57 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_rd_sort(DirectArgs R) {
   atomicMin(&s_min, (unsigned long long)cmin);
   atomicMax(&s_max, (unsigned long long)cmax);
   __syncthreads();
-  const bool crowd = blockIdx.x == 1 && s_sq > (uint64_t)CROWDED * (uint64_t)max(S.n, S.n * S.n / S.nbk);
+  bool crowd = blockIdx.x == 1 && s_sq > (uint64_t)CROWDED * (uint64_t)max(S.n, S.n * S.n / S.nbk);
+  // Rows that crowd make crowds of products of columns that do not: when one
+  // bucket of columns could give an interval several times its products, a
+  // sorted sample of the products tells whether any interval has them.
+  const bool look = blockIdx.x == 1 && (crowd || (uint64_t)s_most * (uint64_t)R.set[0].n > R.peak);
+  if (look) {   // the same for every thread
+    int64_t* key = reinterpret_cast<int64_t*>(hist);   // (start[] has the buckets)
+    const DirectSet& A = R.set[0];
+    __syncthreads();
+    for (int o = tid; o < R.ncrowd; o += SORT_BLOCK)
+      key[o] = set_code(A, sample_of(o, 0, A.n), &err) +
+               set_code(S, sample_of(o, DIRECT_CROWD_CELLS, S.n), &err);
+    __syncthreads();
+    block_sort<SORT_BLOCK>(key, R.ncrowd);
+    uint32_t near = 0;
+    for (int o = tid; o + R.nnear <= R.ncrowd; o += SORT_BLOCK) {
+      const int64_t c = key[o] >> R.cw;
+      const uint32_t c0 = first_from(key, 0, o, c << R.cw);
+      const uint32_t c1 = first_from(key, o, R.ncrowd, (c + 1) << R.cw);
+      near |= (double)(key[o + R.nnear - 1] - key[o]) * (double)(c1 - c0) <= R.near ? 1u : 0u;
+    }
+    near = block_or<SORT_BLOCK>(near);
+    crowd = crowd || near != 0;
+    if (crowd)
+      for (int o = tid; o <= R.ncrowd; o += SORT_BLOCK)
+        R.bounds[o] = o == 0 ? 0 : o == R.ncrowd ? R.ncodes : key[o];
+  }
   if (tid == 0) {
     R.meta->set_err[blockIdx.x] = err;
     R.meta->set_min[blockIdx.x] = s_min;
     R.meta->set_max[blockIdx.x] = s_max;
     if (blockIdx.x == 1) R.meta->crowd = crowd ? 1u : 0u;
   }
-  if (S.n <= DIRECT_PLACE) {
-    for (int64_t i = tid; i < S.n; i += SORT_BLOCK) {
-      const int64_t code = set_code(S, i, &err);
-      const int64_t at = hist[code >> S.shift] + S.rank[i];
-      if (crowd) {
-        R.tmp_k[at] = code;
-        R.tmp_i[at] = (int32_t)i;
-      } else {
-        place_term(R, S, i, code, at);
-      }
+  if (S.n > DIRECT_PLACE) return;
+  const int32_t* start = look ? S.start : hist;
+  for (int64_t i = tid; i < S.n; i += SORT_BLOCK) {
+    const int64_t code = set_code(S, i, &err);
+    const int64_t at = start[code >> S.shift] + S.rank[i];
+    if (crowd) {
+      R.tmp_k[at] = code;
+      R.tmp_i[at] = (int32_t)i;
+    } else {
+      place_term(R, S, i, code, at);
     }
   }
   if (!crowd) return;
   __syncthreads();
-  if (S.n <= DIRECT_PLACE)
-    for (int64_t t = tid; t < S.n; t += SORT_BLOCK) {
-      const int64_t b = R.tmp_k[t] >> S.shift;
-      place_sorted(R, S, t, hist[b], b + 1 < S.nbk ? hist[b + 1] : (int32_t)S.n);
-    }
-  __syncthreads();   // hist has been read
-  int64_t* key = reinterpret_cast<int64_t*>(hist);
-  const DirectSet& A = R.set[0];
-  for (int o = tid; o < R.ncrowd; o += SORT_BLOCK)
-    key[o] = set_code(A, sample_of(o, 0, A.n), &err) +
-             set_code(S, sample_of(o, DIRECT_CROWD_CELLS, S.n), &err);
-  __syncthreads();
-  block_sort<SORT_BLOCK>(key, R.ncrowd);
-  for (int o = tid; o <= R.ncrowd; o += SORT_BLOCK)
-    R.bounds[o] = o == 0 ? 0 : o == R.ncrowd ? R.ncodes : key[o];
+  for (int64_t t = tid; t < S.n; t += SORT_BLOCK) {
+    const int64_t b = R.tmp_k[t] >> S.shift;
+    place_sorted(R, S, t, S.start[b], S.start[b + 1]);
+  }
 }
 
 __global__ void __launch_bounds__(SMALL_BLOCK) k_rd_place(DirectArgs R) {
@@ -357,17 +380,40 @@ __global__ void __launch_bounds__(PLAN_BLOCK) k_rd_plan(DirectArgs R) {
       *hi = min(R.ncodes, *lo + ((int64_t)1 << R.cw));
     }
   };
-  const auto units_of = [&](int64_t c) -> int64_t {
-    const int64_t n = R.ccount[c];
-    int64_t k = n ? (n + t - 1) / t : 0;
-    if (!crowd || k == 0) return min(k, (int64_t)1 << R.cw);
-    int64_t lo, hi;
-    cell_of(c, &lo, &hi);
-    if (!R.wide_codes) k = max(k, (hi - lo + ((int64_t)1 << 31) - 1) >> 31);
-    return min(k, hi - lo);
+  // Intervals of this thread's cells: each(lo, end, k) takes the codes [lo, end),
+  // cut into k.  A cell is cut by its own products; sampled cells, which are
+  // uneven, are taken together while they fill one interval.
+  const auto each_run = [&](auto&& each) {
+    int64_t lo = 0, end = 0, sum = 0;   // sampled cells taken together
+    for (int64_t c = c0; c < c1; ++c) {
+      const int64_t n = R.ccount[c];
+      if (n == 0) continue;
+      int64_t l, h, k = (n + t - 1) / t;
+      cell_of(c, &l, &h);
+      if (h <= l) continue;
+      const int64_t most = R.wide_codes ? INT64_MAX : (int64_t)1 << 31;
+      if (crowd) {
+        if (sum && sum + n <= t && h - lo <= most) {
+          sum += n;
+          end = h;
+          continue;
+        }
+        if (sum) each(lo, end, (int64_t)1);
+        sum = 0;
+        if (!R.wide_codes) k = max(k, (h - l + most - 1) / most);
+        if (k == 1) {
+          lo = l;
+          end = h;
+          sum = n;
+          continue;
+        }
+      }
+      each(l, h, min(k, h - l));
+    }
+    if (sum) each(lo, end, (int64_t)1);
   };
   int64_t mine = 0;
-  for (int64_t c = c0; c < c1; ++c) mine += units_of(c);
+  each_run([&](int64_t, int64_t, int64_t k) { mine += k; });
   int64_t incl = mine;
   for (int off = 1; off < 64; off <<= 1) {
     const int64_t y = __shfl_up(incl, off);
@@ -381,20 +427,16 @@ __global__ void __launch_bounds__(PLAN_BLOCK) k_rd_plan(DirectArgs R) {
     if (w < wave) run += s_ws[w];
     total += s_ws[w];
   }
-  // this workgroup writes the intervals of the cells c with c % grid == block
-  for (int64_t c = c0; c < c1; ++c) {
-    const int64_t k = units_of(c);
-    if (c % gridDim.x == blockIdx.x && k > 0) {
-      int64_t lo, hi;
-      cell_of(c, &lo, &hi);
-      const int64_t step = (hi - lo + k - 1) / k;
+  // this workgroup writes the intervals of every gridDim.x-th thread
+  if (tid % gridDim.x == blockIdx.x)
+    each_run([&](int64_t lo, int64_t end, int64_t k) {
+      const int64_t step = (end - lo + k - 1) / k;
       for (int64_t u = 0; u < k; ++u) {
-        const int64_t a = min(hi, lo + u * step), z = min(hi, a + step);
+        const int64_t a = min(end, lo + u * step), z = min(end, a + step);
         R.units[run + u] = make_longlong2(a, z - a);
       }
-    }
-    run += k;
-  }
+      run += k;
+    });
   if (blockIdx.x == 0 && tid == 0) {
     R.meta->err = R.meta->set_err[0] | R.meta->set_err[1];
     R.meta->out_count = 0;

@@ -661,6 +661,10 @@ constexpr int64_t DIRECT_LOPSIDED = 50;   // columns per row
 // 3.5 ms for this many in one bucket.
 constexpr int64_t DIRECT_COLUMNS = 1 << 18;
 constexpr int DIRECT_CROWD_CELLS = 8192;   // sampled cells at most
+// Samples that stand for a crowd of products when they lie closer together than
+// an interval of their cell is wide: eight times an interval's share, at least
+// this many (spread products have such a dozen in one of a hundred calls).
+constexpr int DIRECT_NEAR = 12;
 // A factor's terms by bucket of their code.
 struct DirectSet {
   const int64_t* k_in; const uint64_t* c_in;
@@ -683,6 +687,9 @@ struct DirectArgs {
   int64_t target, max_units;     // products per interval, intervals at most
   int64_t grid;                  // intervals of a product whose columns are not crowded, at most
   // for crowded columns: cells of sampled bounds, codes and terms by bucket
+  int64_t peak;                  // products of one bucket of columns that make a sample worth it
+  double near;                   // products crowd when nnear samples lie closer than this
+  int32_t nnear;                 // over the samples of their cell
   int32_t ncrowd;                // cells then, a power of two
   int64_t* bounds;               // [ncrowd + 1]
   int64_t* tmp_k; int32_t* tmp_i;   // [terms of the columns]
