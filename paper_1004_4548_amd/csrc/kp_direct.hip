@@ -822,6 +822,8 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
                 if (lane == (((int)__builtin_ctzll(turned) + (int)z) & 63))
                   s_sample[(wave + NW * (products >> 6)) & (CUT_SAMPLES - 1)] = key;
               }
+              // (crowds may share one cell: what is shared is not marked again)
+              if (CROWDS && ok && (shared[cell >> 5] & bit) != 0) continue;
               if (ok && (atomicOr(&marked[cell >> 5], bit) & bit)) atomicOr(&shared[cell >> 5], bit);
               continue;
             }
@@ -991,20 +993,37 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
     for (int r = 0; r < WORDS / NT; ++r)
       alone += __popc(marked[r * NT + tid] & ~shared[r * NT + tid]);
     uint32_t before;
-    alone = total_of(alone, &before);
+    alone = uniform(total_of(alone, &before));
     reserve(alone);
     if (tid == 0) s_next = 0;
     __syncthreads();
+    // The table takes the others if their codes fit.  Terms that repeat and
+    // dense rows have several products a code (stretches sized by the products
+    // would look at every row that many times more): c codes mark m of M cells
+    // when c = -M log(1 - m / M), here to the second power of m / M < 1 / 4.
     const uint32_t others = products - alone;
-    const bool add = others <= (uint32_t)SLOTS * 7 / 8;
-    walk(std::integral_constant<int, 1>{}, 0, width, add);
+    uint32_t codes = others;
+    bool add = others <= (uint32_t)SLOTS * 7 / 8;
+    if (!add) {
+      uint32_t cells = 0;
+      for (int r = 0; r < WORDS / NT; ++r) cells += __popc(marked[r * NT + tid]);
+      cells = total_of(cells, &before);
+      __syncthreads();
+      cells = uniform(cells);
+      const uint32_t twice = (uint32_t)(((uint64_t)cells * cells) >> (MLOG + 1));   // m^2 / 2 M
+      const uint32_t more = (uint32_t)(((uint64_t)twice * cells) >> MLOG) * 2 / 3;   // m^3 / 3 M^2
+      codes = min(others, cells - alone + twice + more + 1);
+      add = codes <= (uint32_t)SLOTS * 3 / 4;
+    }
+    if (add || alone) walk(std::integral_constant<int, 1>{}, 0, width, add);
+    else if (stats && tid == 0) ins += products;
     __syncthreads();
     if (add && !s_over) {
       if (others) emit();
       __syncthreads();
       continue;
     }
-    const uint32_t parts = others / (SLOTS * 5 / 8) + 1;
+    const uint32_t parts = codes / (SLOTS * 5 / 8) + 1;
     const K step = (width + parts - 1) / parts;
     for (K w0 = 0; w0 < width; w0 += step) {
       __syncthreads();

@@ -68,3 +68,26 @@ def test_even_gaps(n, gap, kind):
     got, exp = np.lexsort(ge.T), np.lexsort(at.T)
     assert len(gc) == len(want)
     assert (ge[got] == at[exp]).all() and (gc[got] == want[exp]).all()
+
+
+@pytest.mark.parametrize("kind", ["i64", "f64", "exact"])
+@pytest.mark.parametrize("terms,copies,hi", [(60, 20, 400), (700, 3, 400), (2300, 2, 2000),
+                                             (90, 25, 2000)])
+def test_several_products_per_code(terms, copies, hi, kind):
+    """Spread terms that repeat: an interval's codes fit its table though its
+    products are many times more, fill it, or take several stretches."""
+    print("[case] repeated, spread:", terms, "x", copies, kind, flush=True)
+    rng = np.random.default_rng([terms, copies])
+    e = np.repeat(rng.integers(0, hi, (terms, 5)), copies, 0).astype(np.int32)
+    c = rng.standard_normal(len(e)) if kind == "f64" else rng.integers(-999, 1000, len(e))
+    order = rng.permutation(len(e))
+    a, b = (e, c), (e[order], c[order])
+    ge, gc = _mul(a, b, kind)
+    oe, oc, oab = O.laurent_mul(*a, *b, threads=8, **({"exact": True} if kind == "exact" else {}))
+    if kind == "f64":
+        assert_tolerance([ge], gc, [oe], oc, oab, TOL, "repeated")
+    elif kind == "exact":
+        for w in (0, 1):
+            assert_exact([ge], gc[:, w], [oe], np.asarray(oc)[:, w], f"repeated, word {w}")
+    else:
+        assert_exact([ge], gc, [oe], oc, "repeated")
