@@ -18,15 +18,20 @@
 namespace kp {
 
 constexpr int CUT_SAMPLES = 64;   // offsets that a cut looks at, at most
-constexpr int CUT_PIECES = 9;     // pieces of a cut, at most
+constexpr int CUT_PIECES = 9;     // pieces of a cut, at most (one more than its parts)
 constexpr int CUT_FEW = 16;       // fewer samples than this: equally wide pieces
 
 // Stack entries and log2 of the width that is not cut any more, for the
 // products found from the sorted factors and for packs.  An interval that only
 // equal cuts are left for takes 7 * cut_levels + 1 entries: 134 and 120 for
-// 2^62 codes; the rest is room for sampled cuts, one that takes eight entries.
+// 2^62 codes; the rest is room for sampled cuts, one that takes as many as it
+// has points.
 constexpr int DIRECT_STACK = 144, DIRECT_DONE_LOG = 6;
 constexpr int PACK_STACK = 176, PACK_DONE_LOG = 11;
+// Parts of a sampled cut.  A pack's samples are keys of a full table, the
+// products of the rows walked so far: quartiles, since octiles make pieces of
+// 250 products (a batch of 24 products, some crowded, 695 us instead of 617).
+constexpr int DIRECT_PARTS = 8, PACK_PARTS = 4;
 
 // Equal cuts in eight that lead from width codes to at most 2^done.
 KP_CUT_FN int cut_levels(uint64_t width, int done) {
@@ -41,19 +46,21 @@ KP_CUT_FN int cut_levels(uint64_t width, int done) {
 // how many.  get(i): offset i of n products in the interval, ascending (they
 // may repeat).
 //
-// The cut is at the octiles of the samples, since products that crowd on
-// several scales would take a cut per scale, with two additions:
-//  * It is also cut in the middle, so that a piece has at most half of the
-//    codes, whatever the samples are: cuts end.
-//  * Octiles that coincide at a code that many products share cut that code
+// The cut is at the quantiles of the samples (into `parts`, at most eight),
+// since products that crowd on several scales would take a cut per scale, with
+// two additions:
+//  * When a piece would keep more than seven eighths of the codes, it is also
+//    cut in the middle of the interval: whatever the samples are, cuts end.
+//  * Quantiles that coincide at a code that many products share cut that code
 //    off as a piece of its own.
 // A sampled cut is made only if equal cuts of a piece that follows would still
-// fit the stack; otherwise the cut is equal.  So every entry, at index i with
-// w codes, keeps i + 7 * cut_levels(w) + 1 <= stack: an equal cut adds seven
-// entries and takes a level off.  (Widths are at most 2^62.)
+// fit the stack; otherwise the cut is equal, in eight.  So every entry, at index
+// i with w codes, keeps i + 7 * cut_levels(w) + 1 <= stack: an equal cut adds
+// seven entries and takes a level off.  (Widths are at most 2^62.)
 template <typename K, typename Get, typename Put>
-KP_CUT_FN int cut_points(Get&& get, int n, K width, int sp, int stack, int done, Put&& put) {
-  const K half = width / 2;
+KP_CUT_FN int cut_points(Get&& get, int n, K width, int sp, int stack, int done, int parts,
+                         Put&& put) {
+  const K half = width / 2, most = width - width / 8;
   K from = 0;   // where the last piece begins
   int m = 0;
   const auto next = [&](K x) {
@@ -62,17 +69,25 @@ KP_CUT_FN int cut_points(Get&& get, int n, K width, int sp, int stack, int done,
       from = x;
     }
   };
-  if (n >= CUT_FEW &&
-      sp + CUT_PIECES - 1 + 7 * cut_levels((uint64_t)(width - half), done) + 1 <= stack) {
-    K before = 0;   // the octile before
+  if (n >= CUT_FEW && sp + parts + 7 * cut_levels((uint64_t)most + 1, done) + 1 <= stack) {
+    bool mid = false;
+    K before = 0;   // the quantile before
     KP_CUT_ROLLED
-    for (int i = 1; i < 8; ++i) {
-      const K q = get(i * n / 8), point = q + ((i > 1 ? q == before : q == 0) ? 1 : 0);
+    for (int i = 1; i < parts; ++i) {
+      const K q = get(i * n / parts);
+      mid = mid || q - before > most;
       before = q;
-      if (point > half) next(half);   // (not again once a piece begins there or later)
+    }
+    mid = mid || width - before > most;
+    before = 0;
+    KP_CUT_ROLLED
+    for (int i = 1; i < parts; ++i) {
+      const K q = get(i * n / parts), point = q + ((i > 1 ? q == before : q == 0) ? 1 : 0);
+      before = q;
+      if (mid && point > half) next(half);   // (not again once a piece begins there or later)
       next(point);
     }
-    next(half);
+    if (mid) next(half);
   } else {
     const K step = width / 8 + (width % 8 != 0 ? 1 : 0);
     KP_CUT_ROLLED
