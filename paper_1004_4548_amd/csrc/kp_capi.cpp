@@ -638,9 +638,6 @@ DirectArgs direct_args(const Plan& p, kp_dtype dt, const kp_layout* L, const Dir
   R.max_units = p.dunits;
   R.grid = p.dgrid;
   R.peak = p.dpeak;
-  const double share = (double)p.dtarget * (double)p.dncrowd / ((double)na * (double)nb);
-  R.near = std::ldexp(share, p.dcw);
-  R.nnear = (int32_t)std::max((double)DIRECT_NEAR, std::min(1e6, std::ceil(8.0 * share)));
   R.ncrowd = (int32_t)p.dncrowd;
   R.bounds = d.bounds;
   R.tmp_k = d.tmp_k;

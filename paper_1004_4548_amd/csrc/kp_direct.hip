@@ -59,19 +59,6 @@ __device__ __forceinline__ uint32_t mix(uint64_t k) {
   return mix((uint32_t)k ^ mix((uint32_t)(k >> 32)));
 }
 
-template <int NT>
-__device__ __forceinline__ uint32_t block_or(uint32_t v) {
-  __shared__ uint32_t s_or;
-  if (threadIdx.x == 0) s_or = 0;
-  __syncthreads();
-  v = wave_or(v);
-  if ((threadIdx.x & 63) == 0 && v) atomicOr(&s_or, v);
-  __syncthreads();
-  const uint32_t r = s_or;
-  __syncthreads();
-  return r;
-}
-
 // ------------------------------------------------------------ sorted sets
 // Code of term i of a set, checked against the set's box.
 __device__ __forceinline__ int64_t set_code(const DirectSet& S, int64_t i, uint32_t* err) {
@@ -158,9 +145,10 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_rd_sort(DirectArgs R) {
     sq += (uint64_t)v * v;
   }
   if (lane == 0) s_ws[wave] = sum;
-  if (blockIdx.x == 1 && sq) {
-    atomicAdd(&s_sq, (unsigned long long)sq);
-    atomicMax(&s_most, most);
+  if (blockIdx.x == 1 && sq) atomicAdd(&s_sq, (unsigned long long)sq);
+  if (blockIdx.x == 1) {
+    most = lane_value(wave_scan_max(most), 63);
+    if (lane == 0) atomicMax(&s_most, most);
   }
   __syncthreads();
   uint32_t run = 0;
@@ -199,18 +187,12 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_rd_sort(DirectArgs R) {
                set_code(S, sample_of(o, DIRECT_CROWD_CELLS, S.n), &err);
     __syncthreads();
     block_sort<SORT_BLOCK>(key, R.ncrowd);
-    uint32_t near = 0;
-    for (int o = tid; o + R.nnear <= R.ncrowd; o += SORT_BLOCK) {
-      const int64_t c = key[o] >> R.cw;
-      const uint32_t c0 = first_from(key, 0, o, c << R.cw);
-      const uint32_t c1 = first_from(key, o, R.ncrowd, (c + 1) << R.cw);
-      near |= (double)(key[o + R.nnear - 1] - key[o]) * (double)(c1 - c0) <= R.near ? 1u : 0u;
-    }
-    near = block_or<SORT_BLOCK>(near);
-    crowd = crowd || near != 0;
+    const double pairs = (double)R.set[0].n * (double)S.n;
+    const bool near = samples_crowd<SORT_BLOCK>(key, R.ncrowd, R.cw, (double)R.target, pairs);
+    crowd = crowd || near;
     if (crowd)
       for (int o = tid; o <= R.ncrowd; o += SORT_BLOCK)
-        R.bounds[o] = o == 0 ? 0 : o == R.ncrowd ? R.ncodes : key[o];
+        R.bounds[o] = sample_bound(key, R.ncrowd, o, R.ncodes);
   }
   if (tid == 0) {
     R.meta->set_err[blockIdx.x] = err;
@@ -383,34 +365,14 @@ __global__ void __launch_bounds__(PLAN_BLOCK) k_rd_plan(DirectArgs R) {
   // Intervals of this thread's cells: each(lo, end, k) takes the codes [lo, end),
   // cut into k.  A cell is cut by its own products; sampled cells, which are
   // uneven, are taken together while they fill one interval.
+  const int64_t most = R.wide_codes ? INT64_MAX : (int64_t)1 << 31;
   const auto each_run = [&](auto&& each) {
-    int64_t lo = 0, end = 0, sum = 0;   // sampled cells taken together
-    for (int64_t c = c0; c < c1; ++c) {
-      const int64_t n = R.ccount[c];
-      if (n == 0) continue;
-      int64_t l, h, k = (n + t - 1) / t;
-      cell_of(c, &l, &h);
-      if (h <= l) continue;
-      const int64_t most = R.wide_codes ? INT64_MAX : (int64_t)1 << 31;
-      if (crowd) {
-        if (sum && sum + n <= t && h - lo <= most) {
-          sum += n;
-          end = h;
-          continue;
-        }
-        if (sum) each(lo, end, (int64_t)1);
-        sum = 0;
-        if (!R.wide_codes) k = max(k, (h - l + most - 1) / most);
-        if (k == 1) {
-          lo = l;
-          end = h;
-          sum = n;
-          continue;
-        }
-      }
-      each(l, h, min(k, h - l));
-    }
-    if (sum) each(lo, end, (int64_t)1);
+    each_interval(c0, c1, crowd, t, most, cell_of, [&](int64_t c) { return R.ccount[c]; },
+                  [&](int64_t n, int64_t width) {
+                    const int64_t k = (n + t - 1) / t;
+                    return crowd && !R.wide_codes ? max(k, (width - 1) / most + 1) : k;
+                  },
+                  each);
   };
   int64_t mine = 0;
   each_run([&](int64_t, int64_t, int64_t k) { mine += k; });

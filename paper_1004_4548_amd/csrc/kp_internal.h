@@ -284,6 +284,75 @@ __device__ __forceinline__ void block_sort(int64_t* key, int n) {
       __syncthreads();
     }
 }
+template <int NT>
+__device__ __forceinline__ uint32_t block_or(uint32_t v) {
+  __shared__ uint32_t s_or;
+  if (threadIdx.x == 0) s_or = 0;
+  __syncthreads();
+  v = wave_or(v);
+  if ((threadIdx.x & 63) == 0 && v) atomicOr(&s_or, v);
+  __syncthreads();
+  const uint32_t r = s_or;
+  __syncthreads();
+  return r;
+}
+// Whether products crowd, from n sorted codes of sampled ones (of `pairs` in
+// all): some stretch of a cell of 2^cw codes, as wide as its intervals of
+// `target` products are when they are equally wide, holds eight times that many
+// (and at least a dozen samples, which spread products have in one of a hundred
+// calls).  The workgroup's NT threads call it together after a barrier.
+template <int NT>
+__device__ __forceinline__ bool samples_crowd(const int64_t* key, int n, int cw, double target,
+                                              double pairs) {
+  const double share = target * (double)n / pairs;   // samples of such an interval
+  const int m = (int)fmin(1e6, fmax(12.0, ceil(8.0 * share)));
+  const double most = ldexp(share, cw);
+  uint32_t near = 0;
+  for (int o = threadIdx.x; o + m <= n; o += NT) {
+    const int64_t c = key[o] >> cw;
+    const uint32_t c0 = first_from(key, 0, o, c << cw), c1 = first_from(key, o, n, (c + 1) << cw);
+    near |= (double)(key[o + m - 1] - key[o]) * (double)(c1 - c0) <= most ? 1u : 0u;
+  }
+  return block_or<NT>(near) != 0;
+}
+// Bound o of n cells from n sorted samples: a code that is sampled more than
+// once (many products share it) gets a cell of its own.
+__device__ __forceinline__ int64_t sample_bound(const int64_t* key, int n, int o, int64_t ncodes) {
+  if (o == 0 || o == n) return o == 0 ? 0 : ncodes;
+  return key[o] + (key[o] == key[o - 1] ? 1 : 0);
+}
+// The intervals of the cells [c0, c1): each(lo, end, k) takes the codes [lo, end),
+// cut into k.  count(c) products lie in cell c, units(n, width) intervals hold n
+// of them; `merge` takes cells together while they hold at most `target` products
+// in at most `most` codes.
+template <typename Cell, typename Count, typename Units, typename Each>
+__device__ __forceinline__ void each_interval(int64_t c0, int64_t c1, bool merge, int64_t target,
+                                              int64_t most, Cell&& cell, Count&& count,
+                                              Units&& units, Each&& each) {
+  int64_t lo = 0, end = 0, sum = 0;   // cells taken together
+  for (int64_t c = c0; c < c1; ++c) {
+    const int64_t n = count(c);
+    int64_t l, h;
+    cell(c, &l, &h);
+    if (n <= 0 || h <= l) continue;
+    if (merge && sum && sum + n <= target && h - lo <= most) {
+      sum += n;
+      end = h;
+      continue;
+    }
+    const int64_t k = min(units(n, h - l), h - l);
+    if (merge && sum) each(lo, end, (int64_t)1);
+    sum = 0;
+    if (merge && k == 1) {
+      lo = l;
+      end = h;
+      sum = n;
+    } else {
+      each(l, h, k);
+    }
+  }
+  if (sum) each(lo, end, (int64_t)1);
+}
 // An index below n from a counter, evenly spread.
 __device__ __forceinline__ int64_t sample_of(uint32_t i, uint32_t seed, int64_t n) {
   uint32_t h = (i + seed) * 0x9E3779B1u;
@@ -661,10 +730,6 @@ constexpr int64_t DIRECT_LOPSIDED = 50;   // columns per row
 // 3.5 ms for this many in one bucket.
 constexpr int64_t DIRECT_COLUMNS = 1 << 18;
 constexpr int DIRECT_CROWD_CELLS = 8192;   // sampled cells at most
-// Samples that stand for a crowd of products when they lie closer together than
-// an interval of their cell is wide: eight times an interval's share, at least
-// this many (spread products have such a dozen in one of a hundred calls).
-constexpr int DIRECT_NEAR = 12;
 // A factor's terms by bucket of their code.
 struct DirectSet {
   const int64_t* k_in; const uint64_t* c_in;
@@ -688,8 +753,6 @@ struct DirectArgs {
   int64_t grid;                  // intervals of a product whose columns are not crowded, at most
   // for crowded columns: cells of sampled bounds, codes and terms by bucket
   int64_t peak;                  // products of one bucket of columns that make a sample worth it
-  double near;                   // products crowd when nnear samples lie closer than this
-  int32_t nnear;                 // over the samples of their cell
   int32_t ncrowd;                // cells then, a power of two
   int64_t* bounds;               // [ncrowd + 1]
   int64_t* tmp_k; int32_t* tmp_i;   // [terms of the columns]
@@ -727,6 +790,7 @@ constexpr int PACK_CROWD_CELLS = 4096; // cells of a task with crowded columns a
 constexpr int PACK_BUCKETS = 16384;    // buckets of a factor at most
 constexpr int PACK_HASHED = 1229;      // products of a hashed interval (60 % of its table)
 constexpr int PACK_DENSE = 4096;       // products of a directly indexed interval
+constexpr int PACK_PEAK = 16 * PACK_HASHED;   // see k_pack_sort
 // A factor's terms by bucket of 2^shift codes (arena).
 struct PackSet {
   int64_t n, maxc;

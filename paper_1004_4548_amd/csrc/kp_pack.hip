@@ -37,6 +37,7 @@ constexpr int PACK_BOX_BLOCK = 1024;
 constexpr int PACK_SORT_BLOCK = 1024;
 constexpr int PACK_SLOTS = 2048;        // of an interval's table in LDS
 constexpr int PACK_STEPS = 2;           // candidates per lane with their loads in flight
+constexpr int PACK_COUNT_GROUPS = 16, PACK_COUNT_QUARTERS = 4;   // of cells and rows, for counting
 constexpr int PACK_MAX_PROBE = 32;      // longer chains: the table counts as full
 constexpr int PACK_PER_CU = 3;          // multiplying workgroups that fit a compute unit (LDS)
 static_assert(PACK_SLOTS == 1 << PACK_DONE_LOG, "an interval the table indexes is not cut");
@@ -122,6 +123,7 @@ __global__ void __launch_bounds__(PACK_SORT_BLOCK) k_pack_sort(void* table) {
   extern __shared__ __align__(8) int32_t hist[];
   __shared__ uint32_t s_ws[PACK_SORT_BLOCK / 64];
   __shared__ unsigned long long s_sq;
+  __shared__ uint32_t s_most;   // columns of the fullest bucket
   const PackView P = view(table);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   for (int u = blockIdx.x; u < 2 * P.h->ntasks; u += gridDim.x) {
@@ -134,7 +136,10 @@ __global__ void __launch_bounds__(PACK_SORT_BLOCK) k_pack_sort(void* table) {
       if (tid == 0) *T.count = 0;
       for (int k = tid; k < T.ncrowd && S.n > 0; k += PACK_SORT_BLOCK) T.cells[k] = 0;
     }
-    if (tid == 0) s_sq = 0;
+    if (tid == 0) {
+      s_sq = 0;
+      s_most = 0;
+    }
     for (int k = tid; k < S.nbk; k += PACK_SORT_BLOCK) hist[k] = 0;
     __syncthreads();
     uint32_t bad = 0;
@@ -159,15 +164,20 @@ __global__ void __launch_bounds__(PACK_SORT_BLOCK) k_pack_sort(void* table) {
     // exclusive scan: each wavefront a contiguous stretch of buckets, 64 at a time
     const int per = (S.nbk + PACK_SORT_BLOCK - 1) / PACK_SORT_BLOCK * 64;
     const int b0 = min(S.nbk, wave * per), b1 = min(S.nbk, b0 + per);
-    uint32_t sum = 0;
+    uint32_t sum = 0, most = 0;
     uint64_t sq = 0;
     for (int b = b0; b < b1; b += 64) {
       const uint32_t v = b + lane < b1 ? (uint32_t)hist[b + lane] : 0u;
       sum += lane_value(wave_scan_add(v), 63);
+      most = max(most, v);
       sq += (uint64_t)v * v;
     }
     if (lane == 0) s_ws[wave] = sum;
     if (role == 1 && sq) atomicAdd(&s_sq, (unsigned long long)sq);
+    if (role == 1) {
+      most = lane_value(wave_scan_max(most), 63);
+      if (lane == 0) atomicMax(&s_most, most);
+    }
     __syncthreads();
     uint32_t run = 0;
     for (int w = 0; w < wave; ++w) run += s_ws[w];
@@ -182,12 +192,35 @@ __global__ void __launch_bounds__(PACK_SORT_BLOCK) k_pack_sort(void* table) {
     // (a product of fewer than 64 codes a pair has directly indexed
     // intervals, or not many times more: simplices share a bucket with 30, and
     // exact intervals cost them 130 us of a batch's 710 for nothing)
-    const bool crowd = role == 1 && T.nkeys / 64 >= S.n * T.set[0].n &&
-                       s_sq > (uint64_t)CROWDED * (uint64_t)max(S.n, S.n * S.n / S.nbk);
+    const int64_t pairs = S.n * T.set[0].n;
+    const bool thin = role == 1 && pairs > 0 && T.nkeys / 64 >= pairs;
+    bool crowd = thin && s_sq > (uint64_t)CROWDED * (uint64_t)max(S.n, S.n * S.n / S.nbk);
+    // Rows that crowd make crowds of products of columns that do not: when one
+    // bucket of columns could give an interval many times its products, a
+    // sample of the products tells whether any has them (random terms, ten to
+    // the fullest bucket, do without up to 2,000 rows).
+    const bool look = crowd || (thin && (int64_t)s_most * T.set[0].n >
+                                            max((int64_t)PACK_PEAK, pairs / 256));
+    if (look) {   // the same for every thread
+      __syncthreads();   // hist has been read (start[] has the buckets)
+      const PackSet& A = T.set[0];
+      int64_t* key = reinterpret_cast<int64_t*>(hist);
+      for (int o = tid; o < T.ncrowd; o += PACK_SORT_BLOCK)
+        key[o] = code_in(isb ? T.la : T.lb, isb ? T.ax : T.bx, A.maxc, sample_of(o, 0, A.n)) +
+                 code_of(sample_of(o, PACK_CROWD_CELLS, S.n));
+      __syncthreads();
+      block_sort<PACK_SORT_BLOCK>(key, T.ncrowd);
+      crowd = samples_crowd<PACK_SORT_BLOCK>(key, T.ncrowd, T.cw, (double)PACK_HASHED,
+                                             (double)pairs) || crowd;
+      if (crowd)
+        for (int o = tid; o <= T.ncrowd; o += PACK_SORT_BLOCK)
+          T.bounds[o] = sample_bound(key, T.ncrowd, o, T.nkeys);
+    }
     if (role == 1 && tid == 0) *T.crowd = crowd ? 1u : 0u;
+    const int32_t* start = look ? S.start : hist;
     for (int64_t r = tid; r < S.n; r += PACK_SORT_BLOCK) {
       const int64_t k = code_of(r);
-      const int64_t at = hist[k >> S.shift] + S.rank[r];
+      const int64_t at = start[k >> S.shift] + S.rank[r];
       if (crowd) {
         T.tmp_k[at] = k;
         T.tmp_i[at] = (int32_t)r;
@@ -226,16 +259,6 @@ __global__ void __launch_bounds__(PACK_SORT_BLOCK) k_pack_sort(void* table) {
         S.c[t] = c[si[t]];
         if (src != S.k) S.k[t] = src[t];
       }
-      __syncthreads();   // hist has been read
-      const PackSet& A = T.set[0];
-      int64_t* key = reinterpret_cast<int64_t*>(hist);
-      for (int o = tid; o < T.ncrowd; o += PACK_SORT_BLOCK)
-        key[o] = code_in(isb ? T.la : T.lb, isb ? T.ax : T.bx, A.maxc, sample_of(o, 0, A.n)) +
-                 code_of(sample_of(o, PACK_CROWD_CELLS, S.n));
-      __syncthreads();
-      block_sort<PACK_SORT_BLOCK>(key, T.ncrowd);
-      for (int o = tid; o <= T.ncrowd; o += PACK_SORT_BLOCK)
-        T.bounds[o] = o == 0 ? 0 : o == T.ncrowd ? T.nkeys : key[o];
     }
     if (bad) atomicOr(&P.h->err, bad);
     __syncthreads();   // the next factor clears hist
@@ -272,15 +295,21 @@ __device__ __forceinline__ void columns_of(const PackSet& B, bool crowd, int64_t
 // The products of each cell of 2^cw codes (whole buckets of the columns: a
 // bound): one workgroup per task, 64 cells and a quarter of the rows, a cell
 // per lane and a slice of the rows per wavefront, four rows' loads in flight.
+// (Sixteen groups of cells for the sake of crowded tasks, which have up to
+// 4,096 cells: with the four of the others one such task of 6,000 x 6,000 terms
+// took 4 ms to count.)
 __global__ void __launch_bounds__(PACK_BLOCK) k_pack_count(void* table) {
-  constexpr int GROUPS = PACK_CELLS / 64, QUARTERS = 4;
+  constexpr int GROUPS = PACK_COUNT_GROUPS, QUARTERS = PACK_COUNT_QUARTERS;
   __shared__ unsigned long long s_count[64];
   const PackView P = view(table);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int units = P.h->ntasks * GROUPS * QUARTERS;
+  constexpr int FIRST = PACK_CELLS / 64;   // groups of a task that is not crowded
+  const int units = P.h->ntasks * GROUPS * QUARTERS, first = P.h->ntasks * FIRST * QUARTERS;
   for (int u = blockIdx.x; u < units; u += gridDim.x) {
-    const PackTask& T = P.tasks[u / (GROUPS * QUARTERS)];
-    const int group = (u / QUARTERS) % GROUPS, quarter = u % QUARTERS;
+    // (the groups that every task has come first)
+    const int v = u < first ? u : u - first, per_task = u < first ? FIRST : GROUPS - FIRST;
+    const PackTask& T = P.tasks[v / (per_task * QUARTERS)];
+    const int group = (v / QUARTERS) % per_task + (u < first ? 0 : FIRST), quarter = v % QUARTERS;
     const int64_t* __restrict__ ak = T.set[0].k;
     const PackSet B = T.set[1];
     const int64_t an = T.set[0].n, per = (an + QUARTERS - 1) / QUARTERS;
@@ -349,31 +378,31 @@ __global__ void __launch_bounds__(PACK_BLOCK) k_pack_plan(void* table) {
     // hashed intervals are made larger when they would outgrow the task's array
     const int64_t room = max((int64_t)1, T.max_units - cells);
     const int64_t target = max((int64_t)PACK_HASHED, (all + room - 1) / room);
-    const auto units_of = [&](int c, int64_t* lo, int64_t* width) -> int64_t {
-      const int64_t m = (int64_t)T.cells[c];
-      int64_t end;
-      cell_of(T, crowd, c, lo, &end);
-      *width = end - *lo;
-      if (m <= 0 || *width <= 0) return 0;
-      const int64_t hashed = (m + target - 1) / target;
-      const int64_t dense = max((m + PACK_DENSE - 1) / PACK_DENSE,
-                                (*width + PACK_SLOTS - 1) / PACK_SLOTS);
-      return min(min(hashed, dense), *width);
+    // (sampled cells, which are uneven, are taken together while they fill one interval)
+    const auto each_run = [&](auto&& each) {
+      each_interval(c0, c1, crowd, target, INT64_MAX,
+                    [&](int64_t c, int64_t* lo, int64_t* end) { cell_of(T, crowd, (int)c, lo, end); },
+                    [&](int64_t c) { return (int64_t)T.cells[c]; },
+                    [&](int64_t m, int64_t width) {
+                      const int64_t dense = max((m + PACK_DENSE - 1) / PACK_DENSE,
+                                                (width + PACK_SLOTS - 1) / PACK_SLOTS);
+                      return min((m + target - 1) / target, dense);
+                    },
+                    each);
     };
-    int64_t lo, width, mine = 0;
-    for (int c = c0; c < c1; ++c) mine += units_of(c, &lo, &width);
+    int64_t mine = 0;
+    each_run([&](int64_t, int64_t, int64_t k) { mine += k; });
     const int64_t total = block_sum(mine, &before);
     if (tid == 0) s_first = (int64_t)atomicAdd(&P.h->nunits, (unsigned long long)total);
     __syncthreads();
     PackUnit* out = P.h->units + s_first + before;
-    for (int c = c0; c < c1; ++c) {
-      const int64_t k = units_of(c, &lo, &width);
-      const int64_t step = k ? (width + k - 1) / k : 0;
+    each_run([&](int64_t lo, int64_t end, int64_t k) {
+      const int64_t width = end - lo, step = (width + k - 1) / k;
       for (int64_t u = 0; u < k; ++u) {
         const int64_t a = min(width, u * step), z = min(width, a + step);
         *out++ = PackUnit{lo + a, z - a, t};
       }
-    }
+    });
     __syncthreads();   // the next task uses s_ws
   }
 }
@@ -677,8 +706,8 @@ hipError_t launch_pack_run(void* table_dev, int max_tasks, int num_cu, hipStream
   const int tasks = std::min(2 * max_tasks, num_cu);
   hipLaunchKernelGGL(k_pack_sort, dim3((unsigned)tasks), dim3(PACK_SORT_BLOCK),
                      (size_t)PACK_BUCKETS * 4, s, table_dev);
-  hipLaunchKernelGGL(k_pack_count, dim3((unsigned)std::min(4 * max_tasks, num_cu) * 4),
-                     dim3(PACK_BLOCK), 0, s, table_dev);
+  const int counts = std::min(PACK_COUNT_GROUPS * PACK_COUNT_QUARTERS * max_tasks, 8 * num_cu);
+  hipLaunchKernelGGL(k_pack_count, dim3((unsigned)counts), dim3(PACK_BLOCK), 0, s, table_dev);
   hipLaunchKernelGGL(k_pack_plan, dim3((unsigned)std::min(max_tasks, num_cu)), dim3(PACK_BLOCK),
                      0, s, table_dev);
   hipLaunchKernelGGL(k_pack_mul, dim3((unsigned)(PACK_PER_CU * num_cu)), dim3(PACK_BLOCK), 0, s,

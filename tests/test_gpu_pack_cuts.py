@@ -44,3 +44,42 @@ def test_every_product_once(na, clumps, f64):
         assert bool((torch.bincount(i * len(u.coef) + k, minlength=len(c)) == 1).all())
         assert bool((r.exps[:, 1] == u.exps[k, 1]).all())
         assert bool((c == a.coef[i] * u.coef[k]).all())
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("shape", ["box rows, clumped columns", "box rows, spread columns",
+                                   "copies and a far term", "copies of one term, far"])
+def test_crowds_match_oracle(shape, f64):
+    """Products that crowd though the columns do not, and codes that many
+    products share: sampled cells, some taken together, some of one code."""
+    import torch
+    import oracle as O
+    from tests.helpers import assert_exact, assert_tolerance
+    print("[case] pack", shape, "f64" if f64 else "i64", flush=True)
+    rng = np.random.default_rng([len(shape), f64])
+    coef = lambda n: rng.standard_normal(n) if f64 else rng.integers(-999, 1000, n)
+    tasks = []
+    for n in (300, 1700):
+        if shape.startswith("box"):
+            flat = rng.choice(15 ** 3, n, replace=False)
+            a = np.stack([flat // 15 ** v % 15 for v in range(3)], axis=1)
+            b = rng.integers(0, 5000, (n + 100, 3))
+            if "clumped" in shape:
+                b[:100] = rng.integers(0, 4990, 3) + rng.integers(0, 8, (100, 3))
+        else:
+            terms = 1 if "one" in shape else 30
+            a = np.repeat(rng.integers(0, 20, (terms, 4)), n // terms, 0)
+            a[0] = 6000
+            b = a[rng.permutation(len(a))]
+        a, b = a.astype(np.int32), b.astype(np.int32)
+        tasks.append((a, coef(len(a)), b, coef(len(b))))
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    p = kp.Pack(4)
+    p.launch([(kp.Poly(dev(a), dev(ca)), kp.Poly(dev(b), dev(cb))) for a, ca, b, cb in tasks])
+    for (a, ca, b, cb), r in zip(tasks, p.wait()):
+        oe, oc, oab = O.laurent_mul(a, ca, b, cb, threads=8)
+        ge, gc = r.exps.cpu().numpy(), r.coef.cpu().numpy()
+        if f64:
+            assert_tolerance([ge], gc, [oe], oc, oab, 1e-13, shape)
+        else:
+            assert_exact([ge], gc, [oe], oc, shape)
