@@ -35,9 +35,7 @@ constexpr int DIRECT_PARTS = 8, PACK_PARTS = 4;
 
 // Equal cuts in eight that lead from width codes to at most 2^done.
 KP_CUT_FN int cut_levels(uint64_t width, int done) {
-  int bits = 0;   // ceil(log2(width))
-  KP_CUT_ROLLED
-  while (((uint64_t)1 << bits) < width) ++bits;
+  const int bits = width <= 1 ? 0 : 64 - __builtin_clzll(width - 1);   // ceil(log2(width))
   return bits <= done ? 0 : (bits - done + 2) / 3;
 }
 
@@ -57,9 +55,9 @@ KP_CUT_FN int cut_levels(uint64_t width, int done) {
 // fit the stack; otherwise the cut is equal, in eight.  So every entry, at index
 // i with w codes, keeps i + 7 * cut_levels(w) + 1 <= stack: an equal cut adds
 // seven entries and takes a level off.  (Widths are at most 2^62.)
-template <typename K, typename Get, typename Put>
-KP_CUT_FN int cut_points(Get&& get, int n, K width, int sp, int stack, int done, int parts,
-                         Put&& put) {
+template <typename K, int PARTS, typename Get, typename Put>
+KP_CUT_FN int cut_points(Get&& get, int n, K width, int sp, int stack, int done, Put&& put) {
+  static_assert(PARTS <= 8, "at most nine pieces");
   const K half = width / 2, most = width - width / 8;
   K from = 0;   // where the last piece begins
   int m = 0;
@@ -69,21 +67,15 @@ KP_CUT_FN int cut_points(Get&& get, int n, K width, int sp, int stack, int done,
       from = x;
     }
   };
-  if (n >= CUT_FEW && sp + parts + 7 * cut_levels((uint64_t)most + 1, done) + 1 <= stack) {
+  if (n >= CUT_FEW && sp + PARTS + 7 * cut_levels((uint64_t)most + 1, done) + 1 <= stack) {
+    K q[PARTS + 1];
+    q[0] = 0;
+    q[PARTS] = width;
+    for (int i = 1; i < PARTS; ++i) q[i] = get(i * n / PARTS);
     bool mid = false;
-    K before = 0;   // the quantile before
-    KP_CUT_ROLLED
-    for (int i = 1; i < parts; ++i) {
-      const K q = get(i * n / parts);
-      mid = mid || q - before > most;
-      before = q;
-    }
-    mid = mid || width - before > most;
-    before = 0;
-    KP_CUT_ROLLED
-    for (int i = 1; i < parts; ++i) {
-      const K q = get(i * n / parts), point = q + ((i > 1 ? q == before : q == 0) ? 1 : 0);
-      before = q;
+    for (int i = 0; i < PARTS; ++i) mid = mid || q[i + 1] - q[i] > most;
+    for (int i = 1; i < PARTS; ++i) {
+      const K point = q[i] + (q[i] == q[i - 1] ? 1 : 0);
       if (mid && point > half) next(half);   // (not again once a piece begins there or later)
       next(point);
     }

@@ -938,9 +938,8 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
         s_sample[rank] = key;
         wave_sync();
         // (the same in every lane)
-        const int m = cut_points<K>([&](int i) { return uniform(s_sample[i]); }, n, width, sp,
-                                    DIRECT_STACK, DIRECT_DONE_LOG, DIRECT_PARTS,
-                                    [&](int p, K x, K y) {
+        const int m = cut_points<K, DIRECT_PARTS>([&](int i) { return uniform(s_sample[i]); }, n, width, sp,
+                                    DIRECT_STACK, DIRECT_DONE_LOG, [&](int p, K x, K y) {
                                       s_lo[sp + p] = lo + (int64_t)x;
                                       s_width[sp + p] = y - x;
                                     });

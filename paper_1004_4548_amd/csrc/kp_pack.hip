@@ -601,8 +601,8 @@ __global__ void __launch_bounds__(PACK_BLOCK, PACK_PER_CU) k_pack_mul(void* tabl
           sorted[rank] = key;
           wave_sync();
           // (the same in every lane)
-          const int m = cut_points<uint64_t>([&](int i) { return uniform(sorted[i]); }, n, width,
-                                             sp, PACK_STACK, PACK_DONE_LOG, PACK_PARTS,
+          const int m = cut_points<uint64_t, PACK_PARTS>([&](int i) { return uniform(sorted[i]); }, n, width,
+                                             sp, PACK_STACK, PACK_DONE_LOG,
                                              [&](int p, uint64_t x, uint64_t y) {
                                                s_lo[sp + p] = lo + (int64_t)x;
                                                s_width[sp + p] = y - x;

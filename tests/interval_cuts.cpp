@@ -41,11 +41,11 @@ static int sample(int kind, K width, K* s) {
 
 static int most_sp = 0, most_cuts = 0;
 
-template <typename K>
-static void check_cut(int kind, K width, int sp, int stack, int done, int parts, K* at, int* m) {
+template <typename K, int PARTS>
+static void check_cut(int kind, K width, int sp, int stack, int done, K* at, int* m) {
   K s[CUT_SAMPLES];
   const int n = sample(kind, width, s);
-  *m = cut_points<K>([&](int i) { return s[i]; }, n, width, sp, stack, done, parts,
+  *m = cut_points<K, PARTS>([&](int i) { return s[i]; }, n, width, sp, stack, done,
                      [&](int p, K x, K y) {
                        at[p] = x;
                        at[p + 1] = y;
@@ -62,8 +62,8 @@ static void check_cut(int kind, K width, int sp, int stack, int done, int parts,
 }
 
 // A path of cuts: the piece that goes on is the widest, the last or any one.
-template <typename K>
-static void path(uint64_t width0, int stack, int done, int parts) {
+template <typename K, int PARTS>
+static void path(uint64_t width0, int stack, int done) {
   K width = (K)width0;
   int sp = 0, cuts = 0;
   const int way = (int)below(4), one = (int)below(10);
@@ -71,7 +71,7 @@ static void path(uint64_t width0, int stack, int done, int parts) {
   while ((uint64_t)width > ((uint64_t)1 << done)) {
     K at[CUT_PIECES + 1];
     int m = 0;
-    check_cut(mixed ? (int)below(10) : one, width, sp, stack, done, parts, at, &m);
+    check_cut<K, PARTS>(mixed ? (int)below(10) : one, width, sp, stack, done, at, &m);
     const auto wide = [&](int p) { return at[p + 1] - at[p]; };
     int p = m - 1;
     if (way == 1) p = (int)below(m);
@@ -89,7 +89,8 @@ static void path(uint64_t width0, int stack, int done, int parts) {
 
 // A whole product: offsets (with repeats) of one interval, cut until a piece
 // has at most `most` of them or 2^done codes; every offset is met once.
-static void whole(std::vector<uint64_t> x, uint64_t width0, size_t most, int stack, int done, int parts,
+template <int PARTS>
+static void whole(std::vector<uint64_t> x, uint64_t width0, size_t most, int stack, int done,
                   bool first_lanes) {
   std::sort(x.begin(), x.end());
   std::vector<uint64_t> lo(stack + CUT_PIECES), width(stack + CUT_PIECES);
@@ -112,7 +113,7 @@ static void whole(std::vector<uint64_t> x, uint64_t width0, size_t most, int sta
     uint64_t s[CUT_SAMPLES];
     for (int i = 0; i < CUT_SAMPLES; ++i) s[i] = first_lanes ? *b - a : *(b + (long)below(k)) - a;
     std::sort(s, s + CUT_SAMPLES);
-    const int m = cut_points<uint64_t>([&](int i) { return s[i]; }, CUT_SAMPLES, w, sp, stack, done, parts,
+    const int m = cut_points<uint64_t, PARTS>([&](int i) { return s[i]; }, CUT_SAMPLES, w, sp, stack, done,
                                        [&](int p, uint64_t v, uint64_t y) {
                                          lo[sp + p] = a + v;
                                          width[sp + p] = y - v;
@@ -130,31 +131,33 @@ static void whole(std::vector<uint64_t> x, uint64_t width0, size_t most, int sta
   }
 }
 
-int main() {
-  for (int done : {DIRECT_DONE_LOG, PACK_DONE_LOG}) {
-    const int stack = done == DIRECT_DONE_LOG ? DIRECT_STACK : PACK_STACK;
-    const int parts = done == DIRECT_DONE_LOG ? DIRECT_PARTS : PACK_PARTS;
-    most_sp = most_cuts = 0;
-    for (int k = 0; k < 100000; ++k) {
-      const int log = done + 1 + (int)below(62 - done);
-      uint64_t w = ((uint64_t)1 << (log - 1)) + 1 + below((uint64_t)1 << (log - 1));
-      if (below(8) == 0) w = (uint64_t)1 << log;
-      path<uint64_t>(w, stack, done, parts);
-      if (w <= ((uint64_t)1 << 31)) path<uint32_t>(w, stack, done, parts);
-    }
-    for (int rep = 0; rep < 20; ++rep) {
-      const uint64_t w = (uint64_t)1 << (20 + 2 * rep);
-      std::vector<uint64_t> heavy(40000, 0), two(40000), many;
-      heavy.push_back(below(w));
-      for (size_t i = 0; i < two.size(); ++i) two[i] = i % 2 ? 100 : 0;
-      for (int i = 0; i < 60000; ++i) many.push_back((w - 1) >> below(60));
-      for (bool first : {false, true}) {
-        whole(heavy, w, 7281, stack, done, parts, first);
-        whole(two, w, 29127, stack, done, parts, first);
-        whole(many, w, 1024, stack, done, parts, first);
-      }
-    }
-    std::printf("done 2^%d: stack %d of %d, %d cuts\n", done, most_sp, stack, most_cuts);
+template <int PARTS>
+static void check(int stack, int done) {
+  most_sp = most_cuts = 0;
+  for (int k = 0; k < 100000; ++k) {
+    const int log = done + 1 + (int)below(62 - done);
+    uint64_t w = ((uint64_t)1 << (log - 1)) + 1 + below((uint64_t)1 << (log - 1));
+    if (below(8) == 0) w = (uint64_t)1 << log;
+    path<uint64_t, PARTS>(w, stack, done);
+    if (w <= ((uint64_t)1 << 31)) path<uint32_t, PARTS>(w, stack, done);
   }
+  for (int rep = 0; rep < 20; ++rep) {
+    const uint64_t w = (uint64_t)1 << (20 + 2 * rep);
+    std::vector<uint64_t> heavy(40000, 0), two(40000), many;
+    heavy.push_back(below(w));
+    for (size_t i = 0; i < two.size(); ++i) two[i] = i % 2 ? 100 : 0;
+    for (int i = 0; i < 60000; ++i) many.push_back((w - 1) >> below(60));
+    for (bool first : {false, true}) {
+      whole<PARTS>(heavy, w, 7281, stack, done, first);
+      whole<PARTS>(two, w, 29127, stack, done, first);
+      whole<PARTS>(many, w, 1024, stack, done, first);
+    }
+  }
+  std::printf("done 2^%d: stack %d of %d, %d cuts\n", done, most_sp, stack, most_cuts);
+}
+
+int main() {
+  check<DIRECT_PARTS>(DIRECT_STACK, DIRECT_DONE_LOG);
+  check<PACK_PARTS>(PACK_STACK, PACK_DONE_LOG);
   return 0;
 }
