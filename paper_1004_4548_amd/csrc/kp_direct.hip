@@ -102,6 +102,24 @@ __device__ __forceinline__ void place_sorted(const DirectArgs& R, const DirectSe
   place_term(R, S, R.tmp_i[t], k, at);
 }
 
+// Sorts the terms [first, first + n) of the crowded columns by bucket in LDS
+// (DIRECT_PLACE at most; `mem` holds twelve bytes for each of their next power
+// of two): the codes at mem, their terms where it returns.  The workgroup calls
+// it together, after a barrier of its own.
+__device__ __forceinline__ const int32_t* sort_chunk(const DirectArgs& R, int64_t first, int n, void* mem) {
+  int size = 1;
+  while (size < n) size <<= 1;
+  int64_t* key = static_cast<int64_t*>(mem);
+  int32_t* term = reinterpret_cast<int32_t*>(key + size);
+  for (int t = threadIdx.x; t < size; t += SORT_BLOCK) {
+    key[t] = t < n ? R.tmp_k[first + t] : INT64_MAX;
+    term[t] = t < n ? R.tmp_i[first + t] : t;
+  }
+  __syncthreads();
+  block_sort_terms<SORT_BLOCK>(key, term, size);
+  return term;
+}
+
 // One workgroup per set: bucket histogram of its codes in LDS, each term's
 // rank in its bucket, bucket starts.  Sets of at most DIRECT_PLACE terms are
 // also placed here (one launch less; more terms than that are placed by many
@@ -198,7 +216,7 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_rd_sort(DirectArgs R) {
     R.meta->set_err[blockIdx.x] = err;
     R.meta->set_min[blockIdx.x] = s_min;
     R.meta->set_max[blockIdx.x] = s_max;
-    if (blockIdx.x == 1) R.meta->crowd = crowd ? 1u : 0u;
+    if (blockIdx.x == 1) R.meta->crowd = !crowd ? 0u : s_most > DIRECT_COUNTED ? 2u : 1u;
   }
   if (S.n > DIRECT_PLACE) return;
   const int32_t* start = look ? S.start : hist;
@@ -214,10 +232,16 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_rd_sort(DirectArgs R) {
   }
   if (!crowd) return;
   __syncthreads();
-  for (int64_t t = tid; t < S.n; t += SORT_BLOCK) {
-    const int64_t b = R.tmp_k[t] >> S.shift;
-    place_sorted(R, S, t, S.start[b], S.start[b + 1]);
+  if (s_most <= DIRECT_COUNTED) {
+    for (int64_t t = tid; t < S.n; t += SORT_BLOCK) {
+      const int64_t b = R.tmp_k[t] >> S.shift;
+      place_sorted(R, S, t, S.start[b], S.start[b + 1]);
+    }
+    return;
   }
+  const int32_t* term = sort_chunk(R, 0, (int)S.n, hist);
+  const int64_t* key = reinterpret_cast<const int64_t*>(hist);
+  for (int t = tid; t < S.n; t += SORT_BLOCK) place_term(R, S, term[t], key[t], t);
 }
 
 __global__ void __launch_bounds__(SMALL_BLOCK) k_rd_place(DirectArgs R) {
@@ -235,14 +259,42 @@ __global__ void __launch_bounds__(SMALL_BLOCK) k_rd_place(DirectArgs R) {
   }
 }
 
-// Crowded columns of more than DIRECT_PLACE terms, sorted (else nothing to do).
+// Crowded columns of more than DIRECT_PLACE terms (else nothing to do), when a
+// bucket is too full to count each term's place: chunks sorted in LDS, then
+// each term's place among the terms of its bucket, found in the sorted chunks
+// that hold some of them.  2 x 2^18 terms, the columns of eight codes, take 1.1
+// ms; counting them took 19 (8.4 through the groups).
+__global__ void __launch_bounds__(SORT_BLOCK) k_rd_chunk(DirectArgs R) {
+  extern __shared__ __align__(8) int32_t hist[];
+  const DirectSet& S = R.set[1];
+  const int64_t first = (int64_t)blockIdx.x * DIRECT_PLACE;
+  if (R.meta->crowd != 2 || S.n <= DIRECT_PLACE || first >= S.n) return;
+  const int n = (int)min(DIRECT_PLACE, S.n - first);
+  const int32_t* term = sort_chunk(R, first, n, hist);
+  const int64_t* key = reinterpret_cast<const int64_t*>(hist);
+  for (int t = threadIdx.x; t < n; t += SORT_BLOCK) {
+    R.tmp_k[first + t] = key[t];
+    R.tmp_i[first + t] = term[t];
+  }
+}
 __global__ void __launch_bounds__(SMALL_BLOCK) k_rd_order(DirectArgs R) {
-  if (!R.meta->crowd) return;
   const DirectSet& S = R.set[1];
   const int64_t t = (int64_t)blockIdx.x * SMALL_BLOCK + threadIdx.x;
-  if (t >= S.n || S.n <= DIRECT_PLACE) return;
-  const int64_t b = R.tmp_k[t] >> S.shift;
-  place_sorted(R, S, t, S.start[b], S.start[b + 1]);
+  if (!R.meta->crowd || t >= S.n || S.n <= DIRECT_PLACE) return;
+  const int64_t k = R.tmp_k[t], b = k >> S.shift, own = t / DIRECT_PLACE;
+  const int64_t b0 = S.start[b], b1 = S.start[b + 1];
+  if (R.meta->crowd == 1) {
+    place_sorted(R, S, t, (int32_t)b0, (int32_t)b1);
+    return;
+  }
+  int64_t at = b0;
+  for (int64_t c = b0 / DIRECT_PLACE; c * DIRECT_PLACE < b1; ++c) {
+    const int64_t lo = max(b0, c * DIRECT_PLACE), hi = min(b1, (c + 1) * DIRECT_PLACE);
+    // (equal codes: those of earlier chunks first)
+    at += c == own ? t - lo
+                   : (int64_t)first_from(R.tmp_k, (uint32_t)lo, (uint32_t)hi, c < own ? k + 1 : k) - lo;
+  }
+  place_term(R, S, R.tmp_i[t], k, at);
 }
 
 // The columns of codes xlo .. xhi: exactly when they are crowded, else their
@@ -1066,12 +1118,16 @@ hipError_t launch_direct(const DirectArgs& R, kp_dtype dt, int64_t* out_n, uint3
   hipError_t e = direct_setup();
   if (e != hipSuccess) return e;
   if (R.ev0) (void)hipEventRecord(R.ev0, s);
-  const int64_t lds = std::max({R.set[0].nbk * 4, R.set[1].nbk * 4, (int64_t)R.ncrowd * 8});
+  int64_t chunk = 1;   // terms of a sorted chunk's array
+  while (chunk < std::min(R.set[1].n, DIRECT_PLACE)) chunk *= 2;
+  const int64_t lds = std::max({R.set[0].nbk * 4, R.set[1].nbk * 4, (int64_t)R.ncrowd * 8, chunk * 12});
   const int64_t rows = R.set[0].n, n = std::max(rows, R.set[1].n);
   hipLaunchKernelGGL(k_rd_sort, dim3(2), dim3(SORT_BLOCK), (size_t)lds, s, R);
   if (n > DIRECT_PLACE) {
     const unsigned blocks = (unsigned)((n + SMALL_BLOCK - 1) / SMALL_BLOCK);
     hipLaunchKernelGGL(k_rd_place, dim3(blocks, 2), dim3(SMALL_BLOCK), 0, s, R);
+    const unsigned chunks = (unsigned)((R.set[1].n + DIRECT_PLACE - 1) / DIRECT_PLACE);
+    hipLaunchKernelGGL(k_rd_chunk, dim3(chunks), dim3(SORT_BLOCK), (size_t)(chunk * 12), s, R);
     hipLaunchKernelGGL(k_rd_order, dim3(blocks), dim3(SMALL_BLOCK), 0, s, R);
   }
   const int64_t groups = (R.ncell + COUNT_CELLS - 1) / COUNT_CELLS;
