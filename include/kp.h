@@ -140,9 +140,9 @@ typedef struct kp_tune {
                                table in HBM; 1 (default) = grouped when the products are
                                at most 4 times the result bound, else the table; sparse
                                Laurent products then need no grouping when the smaller
-                               factor has at most 24,000 terms and the other hash_* and
-                               grouping knobs are at their defaults: each interval's
-                               products are found from the sorted factors (same workspace) */
+                               factor has at most 24,000 terms and hash_grouping is 0:
+                               each interval's products are found from the sorted factors
+                               (same workspace; the knobs of bins have no effect)         */
   int32_t hash_bucket;      /* hash, Laurent, int64/fp64: > 0 selects Section 3.2's bucketed
                                table instead of the above, with this many slots per bucket
                                (1 .. 16): product code e goes to bucket e mod N, where it is

@@ -900,12 +900,10 @@ kp_status make_plan(kp_ctx* ctx, const kp_layout* L, int poisson, kp_dtype dt, k
     HashCarve h;
     carve_hash(c, *p, poisson, na, nb, &h);
     // Straight from the sorted factors for products spread thinly over the
-    // code space, unless a knob asks for a grouped layout; the workspace stays
-    // the grouped layout's, which is larger.
-    const kp_tune& t = ctx->tune;
-    const bool plain = t.hash_partitioned == 1 && t.hash_grouping == 0 &&
-                       t.hash_bin_slots == 4096 && t.hash_max_bin_bits == 10 &&
-                       t.hash_bin_fill == 42;
+    // code space, unless a knob asks for a grouped layout (the size and fill of
+    // bins ask for nothing: there are none here); the workspace stays the
+    // grouped layout's, which is larger.
+    const bool plain = ctx->tune.hash_partitioned == 1 && ctx->tune.hash_grouping == 0;
     // Many more columns than rows, spread less thinly: sorting the columns is
     // much of the work, and products that meet outgrow the small tables.
     // Simplices of six variables: 4,803 x 77 terms 0.205 ms against 0.185 in
