@@ -1407,7 +1407,10 @@ kp_status enqueue_laurent(kp_ctx* ctx, const kp_layout* layout, kp_dtype dtype, 
     H.a_sa = tr.sa;
     H.b_tb = tr.tb;
     if (!empty && timed) std::tie(H.ev0, H.ev1) = timing_pair(ctx);
-    if (!empty && p.direct) {
+    // (Coded factors of 128-bit products keep the groups: the sorted factors
+    // need codes inside their boxes, which exponents and the 8-byte types' ranges
+    // are checked for, while the two-level groups take any codes.)
+    if (!empty && p.direct && (xo || dtype != KP_I128)) {
       Carver k;
       k.base = static_cast<char*>(workspace);
       Meta* meta = k.take<Meta>(1);

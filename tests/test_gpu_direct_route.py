@@ -45,6 +45,30 @@ def _probes(ctx, a, b):
 def test_only_a_grouping_asks_for_groups(ctx, knobs, direct):
     """A tuner's size and fill of the bins leave the route as it is."""
     print("[case] route", knobs, flush=True)
-    a, b = I.config(3, scale=0.1)
+    a, b = I.config(3, scale=0.04)
     ctx.set_tune(**knobs)
     assert (_probes(ctx, a, b) < 0.02) == direct
+
+
+@pytest.mark.parametrize("exact", [False, True])
+def test_codes_outside_a_factors_box(ctx, exact):
+    """The factors of a codes call the other way round: one's codes lie outside
+    the other's box.  Refused for 8-byte types, a product of 128-bit sums."""
+    print("[case] swapped codes", "exact" if exact else "i64", flush=True)
+    rng = np.random.default_rng(17)
+    a = (rng.integers(0, 40, (300, 5)).astype(np.int32), rng.integers(-999, 1000, 300))
+    b = (rng.integers(0, 200, (400, 5)).astype(np.int32), rng.integers(-999, 1000, 400))
+    pa, pb = (kp.Poly(dev(e), dev(c)) for e, c in (a, b))
+    lay = kp.laurent_layout(pa, pb, ctx)
+    assert lay.nkeys >= 64 * 300 * 400
+    ka, kb = kp.encode(lay, 0, pa.exps, ctx=ctx)[0], kp.encode(lay, 1, pb.exps, ctx=ctx)[0]
+    if not exact:
+        with pytest.raises(kp.KPError) as e:
+            kp.mul_laurent_codes(lay, kb, pb.coef, ka, pa.coef, "hash", ctx)
+        assert e.value.status == kp.KP_E_RANGE
+        return
+    codes, coef, _ = kp.mul_laurent_codes(lay, kb, pb.coef, ka, pa.coef, "hash", ctx, exact=True)
+    oe, oc, _ = O.laurent_mul(a[0], a[1], b[0], b[1], threads=4, exact=True)
+    got = kp.decode(lay, codes, ctx=ctx).cpu().numpy()
+    for w in (0, 1):
+        assert_exact([got], coef.cpu().numpy()[:, w], [oe], np.asarray(oc)[:, w], f"word {w}")
