@@ -555,7 +555,7 @@ void range_shape(const kp_layout* L, int64_t na, int64_t nb, int64_t nprod, int 
 // factor of fewer terms) may be at most DIRECT_ROWS.
 bool direct_shape(const kp_ctx* ctx, const kp_layout* L, int64_t na, int64_t nb, Plan* p) {
   const int64_t pairs = sat_mul(na, nb);
-  if (pairs < 1 || pairs > ((int64_t)1 << 32)) return false;
+  if (pairs < 1 || pairs >= ((int64_t)1 << 32)) return false;   // (an interval counts them in 32 bits)
   p->dswap = na > nb;
   const int64_t n[2] = {p->dswap ? nb : na, p->dswap ? na : nb};
   if (n[0] > DIRECT_ROWS || n[1] > DIRECT_COLUMNS) return false;
