@@ -792,6 +792,7 @@ kp_status make_plan(kp_ctx* ctx, const kp_layout* L, int poisson, kp_dtype dt, k
     d.nchunk = std::max<int64_t>(1, (dn + DENSE_CHUNK - 1) / DENSE_CHUNK);
     d.ntiles = std::max<int64_t>(1, (nbd + DENSE_TILE - 1) / DENSE_TILE);
     d.block = ctx->tune.block;
+    d.nvars = L->nx + L->ny;
     d.target_tasks = std::max<int64_t>(1, (int64_t)ctx->num_cu * ctx->tune.tasks_per_cu);
     d.max_tasks = d.target_tasks;
     d.min_work = 512;

@@ -328,7 +328,9 @@ __global__ void __launch_bounds__(PREP_BLOCK) k_dense_prep(PrepArgs args) {
 constexpr int SCATTER_BLOCK = 256;
 // Pairs from which fp64 products sort their terms completely and carry sums
 // from row to row: the sort takes 10 to 18 us, and at this many pairs the sums
-// save about 25.
+// save about 25.  Not for one variable: there a factor is one long run, whose
+// plain adds have no bank conflicts (11,600 terms: 61 us against 78 carried), or
+// has none (12,000 terms in 72,000 codes: 256 us the call against 267).
 constexpr int64_t DENSE_CHAIN_PAIRS = (int64_t)1 << 27;
 
 // Writes every term at its bucket-sorted position; for factor B also the
@@ -1587,7 +1589,7 @@ hipError_t launch_dense_laurent(const DensePlan& P, const DenseBufs& B, kp_dtype
   pa.meta = B.meta;
   pa.is_i64 = dt != KP_F64;
   const bool chain = dt == KP_F64 && !B.a_sa_in &&
-                     (double)B.na * (double)B.nb >= (double)DENSE_CHAIN_PAIRS;
+                     P.nvars > 1 && (double)B.na * (double)B.nb >= (double)DENSE_CHAIN_PAIRS;
   pa.order = chain ? 1 : 0;
   const size_t hist_bytes = (size_t)std::max(P.nbkA, P.nbkB) * 4;
   hipLaunchKernelGGL(k_dense_prep, dim3(2), dim3(PREP_BLOCK), hist_bytes, s, pa);

@@ -538,6 +538,7 @@ struct DensePlan {
   int64_t nbkA, nbkB;    // buckets
   int64_t maxcodeA, maxcodeB;   // largest code of each factor's box
   int32_t block;
+  int32_t nvars;         // variables of the codes (exponents and trigonometric)
 };
 struct DenseBufs {
   Meta* meta;
