@@ -308,6 +308,7 @@ struct Plan {
   bool direct = false, dswap = false, dsmall = false, dwide = false;
   int dcw = 0, dshift[2] = {0, 0};
   int64_t dncell = 0, dtarget = 1, dunits = 0, dgrid = 0, dncrowd = 0, dpeak = 0;
+  int64_t dmeet = 0;   // rows that meet an interval, about
   int64_t dmax[2] = {0, 0}, dnbk[2] = {0, 0};
 };
 
@@ -591,6 +592,10 @@ bool direct_shape(const kp_ctx* ctx, const kp_layout* L, int64_t na, int64_t nb,
   // does little harm below two intervals' products or a compute unit's share;
   // above, products are sampled to see whether they crowd (a sample of 8,192
   // takes 90 us; random terms, some ten to the fullest bucket, do without).
+  // An interval meets the rows of as many codes as it and the columns span
+  // (rows spread evenly).
+  const double span = (double)p->dmax[1] + (double)L->nkeys * (double)p->dtarget / (double)pairs;
+  p->dmeet = (int64_t)((double)n[0] * std::min(1.0, span / ((double)p->dmax[0] + 1.0)));
   p->dpeak = std::max(2 * full, pairs / ctx->num_cu);
   // crowded columns: sampled cells of up to a quarter of an interval, which 32-bit offsets
   // may cut once more per 2^31 codes (at most once per cell of equal width)
@@ -638,6 +643,7 @@ DirectArgs direct_args(const Plan& p, kp_dtype dt, const kp_layout* L, const Dir
   R.max_units = p.dunits;
   R.grid = p.dgrid;
   R.peak = p.dpeak;
+  R.meet = p.dmeet;
   R.ncrowd = (int32_t)p.dncrowd;
   R.bounds = d.bounds;
   R.tmp_k = d.tmp_k;

@@ -591,7 +591,11 @@ __device__ __forceinline__ void each_digit(const DirectArgs& R, const UnitDigits
 // 5,000 products to an interval, took 2.25 ms.
 // K: offsets in an interval, 32 bits, or 64 for products so few that an
 // interval of 2^31 codes would hold next to none.
-template <typename T, typename K, int NT, int MLOG, int SLOTS>
+// FEW: few rows meet an interval, where the columns span little of the code
+// space.  Batches of 64 rows then leave most wavefronts idle: 12,000 x 12,000
+// terms whose columns span a 1,000th of the rows' 14.1 ms instead of 2.1.  (In
+// every kernel the smaller batches cost 4 %: scalar registers are short.)
+template <typename T, typename K, int NT, int MLOG, int SLOTS, bool FEW>
 __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) {
   constexpr int NW = NT / 64, PER = SLOTS / NT, W = sizeof(T) / 8, WORDS = 1 << (MLOG - 5);
   constexpr bool WIDE = sizeof(K) == 8;
@@ -740,31 +744,45 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
                                         : uniform((uint32_t)A.start[(bhi >> A.shift) + 1]);
       // ROWS * 64 rows at a time (lane l holds rows l, 64 + l, ...), all their
       // loads in flight together; a wavefront takes the next batch when it is
-      // done with its last, rows being unequal
+      // done with its last, rows being unequal.  FEW: a batch is fewer rows when
+      // few meet the interval, and one of up to 32 parts of their columns, so
+      // that every wavefront has some.
+      uint32_t batch = ROWS * 64, plog = 0;
+      if constexpr (FEW) {
+        batch = min(batch, (i1 - i0 + 2 * NW - 1) / (2 * NW));
+        while (plog < 5 && (i1 - i0) << plog < 2 * NW * batch) ++plog;
+      }
       for (;;) {
         uint32_t bt = 0;
-        if (lane == 0) bt = atomicAdd(&s_next, (uint32_t)(ROWS * 64));
-        const uint32_t ib = i0 + lane_value(bt, 0);
+        if (lane == 0) bt = atomicAdd(&s_next, FEW ? 1u : batch);
+        bt = lane_value(bt, 0);
+        const uint32_t ib = i0 + (FEW ? (bt >> plog) * batch : bt);
         if (ib >= i1) break;
+        const uint32_t ie = FEW ? min(i1, ib + batch) : i1;
         if (PASS == 0 && *(volatile uint32_t*)&s_products > MOST && width > UNCUT) return;
         if (PASS == 2 && *(volatile uint32_t*)&s_over) return;
         int64_t a[ROWS];
         uint32_t cnt[ROWS], excl[ROWS];
 #pragma unroll
-        for (int u = 0; u < ROWS; ++u) a[u] = A.k64[min(ib + u * 64 + lane, i1 - 1)];
+        for (int u = 0; u < ROWS; ++u) a[u] = A.k64[min(ib + u * 64 + lane, ie - 1)];
 #pragma unroll
         for (int u = 0; u < ROWS; ++u) {
           const int64_t xlo = blo - a[u], xhi = bhi - a[u];
-          const bool in = ib + u * 64 + lane < i1 && xhi >= 0 && xlo <= B.maxc;
+          const bool in = ib + u * 64 + lane < ie && xhi >= 0 && xlo <= B.maxc;
           columns_of(B, CROWDS, xlo, xhi, &excl[u], &cnt[u]);
           cnt[u] = in ? cnt[u] - excl[u] : 0;
+          if (FEW && plog) {   // (at most 2^18 columns)
+            const uint32_t p = bt & ((1u << plog) - 1), n = cnt[u];
+            excl[u] += (n * p) >> plog;
+            cnt[u] = ((n * (p + 1)) >> plog) - ((n * p) >> plog);
+          }
         }
         uint32_t total = 0;
 #pragma unroll
         for (int u = 0; u < ROWS; ++u) {
           const uint32_t incl = wave_scan_add(cnt[u]);
           const uint32_t first_cand = total + incl - cnt[u];
-          const uint32_t i = min(ib + u * 64 + lane, i1 - 1);
+          const uint32_t i = min(ib + u * 64 + lane, ie - 1);
           const uint64_t ca = PASS != 0 || zeros ? A.c[i] : 0;
           rowd[wave][u * 64 + lane] = make_uint4(excl[u] - first_cand, (uint32_t)(a[u] - lo),
                                                  (uint32_t)ca, (uint32_t)(ca >> 32));
@@ -1085,8 +1103,12 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
 
 template <typename T, typename K, int NT, int MLOG, int SLOTS>
 void launch_mul(const DirectArgs& R, hipStream_t s) {
-  hipLaunchKernelGGL((k_rd_mul<T, K, NT, MLOG, SLOTS>), dim3((unsigned)R.grid), dim3(NT), 0, s,
-                     R);
+  if (R.meet < NT)   // less than a batch a wavefront
+    hipLaunchKernelGGL((k_rd_mul<T, K, NT, MLOG, SLOTS, true>), dim3((unsigned)R.grid), dim3(NT), 0,
+                       s, R);
+  else
+    hipLaunchKernelGGL((k_rd_mul<T, K, NT, MLOG, SLOTS, false>), dim3((unsigned)R.grid), dim3(NT),
+                       0, s, R);
 }
 
 // Table slots of large and small intervals, and of large ones of 64-bit offsets.

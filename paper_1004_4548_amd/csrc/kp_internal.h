@@ -780,6 +780,7 @@ struct DirectArgs {
   int64_t* tmp_k; int32_t* tmp_i;   // [terms of the columns]
   int32_t small;                 // small intervals (DIRECT_SMALL_PRODUCTS)
   int32_t wide_codes;            // cells of more than 2^31 codes: 64-bit offsets
+  int64_t meet;                  // rows that meet an interval, about
   longlong2* units;              // [max_units] {first code, codes}
   int64_t* out_k; void* out_c; int64_t out_cap;
   int32_t* out_x;                // optional decoded output
