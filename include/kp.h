@@ -140,7 +140,8 @@ typedef struct kp_tune {
                                table in HBM; 1 (default) = grouped when the products are
                                at most 4 times the result bound, else the table; sparse
                                Laurent products then need no grouping when the smaller
-                               factor has at most 24,000 terms and hash_grouping is 0:
+                               factor has at most 24,000 terms (fewer when most of them
+                               meet an interval of output codes) and hash_grouping is 0:
                                each interval's products are found from the sorted factors
                                (same workspace; the knobs of bins have no effect)         */
   int32_t hash_bucket;      /* hash, Laurent, int64/fp64: > 0 selects Section 3.2's bucketed

@@ -553,7 +553,8 @@ void range_shape(const kp_layout* L, int64_t na, int64_t nb, int64_t nprod, int 
 // Shape of the accumulation straight from the sorted factors; false when the
 // product is outside what its kernels take, or better in groups:
 // every interval looks at every row that meets it, so that the rows (the
-// factor of fewer terms) may be at most DIRECT_ROWS.
+// factor of fewer terms) may be at most DIRECT_ROWS, of which DIRECT_MEET may
+// meet an interval on average.
 bool direct_shape(const kp_ctx* ctx, const kp_layout* L, int64_t na, int64_t nb, Plan* p) {
   const int64_t pairs = sat_mul(na, nb);
   if (pairs < 1 || pairs >= ((int64_t)1 << 32)) return false;   // (an interval counts them in 32 bits)
@@ -584,6 +585,14 @@ bool direct_shape(const kp_ctx* ctx, const kp_layout* L, int64_t na, int64_t nb,
   p->dcw = std::max(0, K - lc);
   p->dncell = (L->nkeys + ((int64_t)1 << p->dcw) - 1) >> p->dcw;
   for (int k = 0; k < 2; ++k) p->dnbk[k] = (p->dmax[k] >> p->dshift[k]) + 1;
+  // Rows and columns spread evenly over spans of ratio r: a product's interval
+  // meets 1 - r / 3 of the rows (r <= 1), or (1 - 1 / 3 r) / r.  (Rows within a
+  // 64th look at the same columns all together, which the caches make up for.)
+  const double r = ((double)p->dmax[0] + 1.0) / ((double)p->dmax[1] + 1.0);
+  const double meet = r < 1.0 / 64 ? 2.0 / 3 : r <= 1 ? 1 - r / 3 : (1 - 1 / (3 * r)) / r;
+  if ((double)n[0] * meet > (double)DIRECT_MEET) return false;
+  const int64_t buckets = std::min(DENSE_MAX_BUCKETS, std::max((int64_t)4096, 2 * n[1]));
+  if (n[0] + n[0] * n[1] / buckets > DIRECT_LOOKS) return false;
   // small products: enough intervals for two rounds of workgroups
   const int64_t wgs = (p->dsmall ? 4 : 1) * (int64_t)ctx->num_cu;
   p->dtarget = std::min(full, std::max<int64_t>(256, pairs / (2 * wgs)));

@@ -736,10 +736,21 @@ hipError_t launch_range(const RangeArgs& R, kp_dtype dt, hipStream_t s);
 constexpr int DIRECT_CELLS_LOG = 18, DIRECT_SMALL_CELLS_LOG = 16;
 constexpr int64_t DIRECT_PRODUCTS = (1 << DIRECT_CELLS_LOG) / 11;
 constexpr int64_t DIRECT_SMALL_PRODUCTS = (1 << DIRECT_SMALL_CELLS_LOG) / 11;
-// Rows up to which every interval may look at every row.  Measured against the
-// range-grouped layout, int64, six variables in [0, 80]: 20,000 x 20,000 terms
-// 8.6 ms against 11.0, 30,000 x 30,000 terms 27.9 ms against 23.7.
-constexpr int64_t DIRECT_ROWS = 24000;
+// Rows at most, and rows that meet an interval of output codes on average
+// (every interval looks at those).  Measured against the range-grouped layout,
+// int64, three to six variables: 20,000 x 20,000 terms of one box (13,300 rows
+// meet) 8.4 to 9.0 ms against 9.6 to 10.5, 23,500 x 23,500 (15,700) 13.2 against
+// 13.4, 30,000 x 30,000 27.9 against 23.7; rows that span half or a third of the
+// columns: 17,000 (14,200) 6.2 against 6.8, 20,000 (16,700, 17,800) 9.5 and 9.8
+// against 9.3, 23,500 (19,600, 20,900) 15.0 and 15.4 against 13.0; columns that
+// span an eighth of the rows, 23,500: 8.6 against 12.9.
+constexpr int64_t DIRECT_ROWS = 24000, DIRECT_MEET = 14500;
+// A row looks at whole buckets of columns, the more the fuller they are: at most
+// this many rows times (1 + columns per bucket).  15,000 x 90,000 terms (56,000)
+// 44 to 45 ms against 50 to 52, 20,000 x 60,000 (57,000) 38 to 39 against 32 to
+// 45, 10,000 x 180,000 (65,000) 71 against 62 to 69, 21,500 x 150,000 (120,000)
+// 174 against 94.
+constexpr int64_t DIRECT_LOOKS = 60000;
 // Rows up to which small intervals win: 200 x 20,000 terms 0.23 ms against
 // 0.41 with large ones, 1,000 x 20,000 0.39 against 0.53, 3,000 x 3,000 0.33
 // against 0.27.
