@@ -15,16 +15,18 @@
 // about `target` products.  Crowded columns (a box that an outlier makes huge),
 // and columns whose products crowd because the rows do, are sorted within their
 // buckets too, so that a row finds exactly the columns of an interval, and the
-// cells are then bounded by a sorted sample of the products: 600 x 900 terms of three variables in [0, 24) and one outlier
-// each would otherwise be one workgroup's, 95 ms instead of 0.34 (0.50 through
-// the groups); 5,000 x 6,000 terms of five variables take 3.6 ms (139 through
-// the groups).
+// cells are then bounded by a sorted sample of the products: 600 x 900 terms of
+// three variables in [0, 24) and one outlier each would otherwise be one
+// workgroup's, 95 ms instead of 0.31 (0.50 through the groups); 5,000 x 6,000
+// terms of five variables take 1.9 ms (141 through the groups); 5,000 rows in a
+// box and 5,000 columns, 400 of them in a clump, 0.73 instead of 4.2 (1.06).
 //
-// Six launches in all (sort, place when a factor is large, count, plan,
-// multiply, finish) against eighteen of the range-grouped layout, which writes
-// every product to HBM once before it is accumulated.  Measured, whole call:
-// 7,919 x 12,347 terms in five variables, fp64, 3.15 -> 1.67 ms; 500 x 500
-// terms, int64, 0.150 -> 0.105 ms.
+// Five launches in all (sort, count, plan, multiply, finish), and three more for
+// a factor of more than 4,096 terms (place, and chunk and order, which end at
+// once unless the columns crowd), against eighteen of the range-grouped layout,
+// which writes every product to HBM once before it is accumulated.  Measured,
+// whole call: 7,919 x 12,347 terms in five variables, fp64, 3.15 -> 1.66 ms; 500
+// x 500 terms, int64, 0.150 -> 0.105 ms.
 #include <algorithm>
 #include <climits>
 #include <type_traits>
@@ -576,13 +578,15 @@ __device__ __forceinline__ void each_digit(const DirectArgs& R, const UnitDigits
 //      open-addressing table, whose nonzero sums are written last.
 // An interval then holds five times the products that a table in the same LDS
 // would, and a row's stretch of the columns is that much longer.
-//   2. When more products share cells than the table takes, they are added one
-//      stretch of codes at a time, halving a stretch that still overflows.
+//   2. When the codes of products that share cells are more than the table
+//      takes, they are added one stretch of codes at a time, halving a stretch
+//      that still overflows.
 // An interval of far more products than planned (codes that crowd in a small
 // part of a cell) is cut into pieces before anything is written.
 //
 // What bounds it: VALU issue and the latency of the chain row -> columns ->
-// cell -> result slot, not bytes.  Of 1.66 ms on 7,919 x 12,347 terms (9.8e7
+// cell -> result slot, not bytes (the vector units are busy 60 % of the time,
+// the LDS 24 %, wavefronts wait 56 % of theirs).  Of 1.66 ms on 7,919 x 12,347 terms (9.8e7
 // products, 2.7 GB of result) the two walks alone take 0.94 ms, adding the
 // shared products 0.20, writing the others 0.54.  One workgroup of 1024
 // threads per compute unit with 2^18 cells beats two of 512 with 2^17 (1.77

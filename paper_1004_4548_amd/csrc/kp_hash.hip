@@ -922,7 +922,7 @@ __global__ void __launch_bounds__((1 << LOG) / BIN_PER_THREAD) k_radix_bins(Radi
     // one compare-and-swap claims an empty slot or returns its key; the
     // probe loop has one exit test and the value is added after it.  A
     // wavefront waits for its longest chain: growing steps keep chains apart
-    // (a truncated product of 4e8 pairs: 0.50 ms instead of 0.55)
+    // (20,011 x 9,973 terms under a cut, 2.0e8 pairs: 0.50 ms instead of 0.55)
     unsigned long long c = atomicCAS(&keys[slot], 0ull, key);
     int q = 0;
 #pragma nounroll
