@@ -595,8 +595,8 @@ __device__ __forceinline__ void each_digit(const DirectArgs& R, const UnitDigits
 // 5,000 products to an interval, took 2.25 ms.
 // K: offsets in an interval, 32 bits, or 64 for products so few that an
 // interval of 2^31 codes would hold next to none.
-// FEW: few rows meet an interval, where the columns span little of the code
-// space.  Batches of 64 rows then leave most wavefronts idle: 12,000 x 12,000
+// FEW: few of the rows meet an interval, where the columns span little of the
+// code space.  Batches of 64 rows then leave most wavefronts idle: 12,000 x 12,000
 // terms whose columns span a 1,000th of the rows' 14.1 ms instead of 2.1.  (In
 // every kernel the smaller batches cost 4 %: scalar registers are short.)
 template <typename T, typename K, int NT, int MLOG, int SLOTS, bool FEW>
@@ -1107,7 +1107,9 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 4) k_rd_mul(DirectArgs R) 
 
 template <typename T, typename K, int NT, int MLOG, int SLOTS>
 void launch_mul(const DirectArgs& R, hipStream_t s) {
-  if (R.meet < NT)   // less than a batch a wavefront
+  // less than a batch a wavefront, and a few of the rows (60 to 250 rows that all
+  // meet an interval take 5 to 9 us longer in parts: 93 against 101, 122 against 132)
+  if (R.meet < NT && 4 * R.meet < R.set[0].n)
     hipLaunchKernelGGL((k_rd_mul<T, K, NT, MLOG, SLOTS, true>), dim3((unsigned)R.grid), dim3(NT), 0,
                        s, R);
   else
