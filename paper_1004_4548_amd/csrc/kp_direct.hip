@@ -108,7 +108,8 @@ __device__ __forceinline__ void place_sorted(const DirectArgs& R, const DirectSe
 // (DIRECT_PLACE at most; `mem` holds twelve bytes for each of their next power
 // of two): the codes at mem, their terms where it returns.  The workgroup calls
 // it together, after a barrier of its own.
-__device__ __forceinline__ const int32_t* sort_chunk(const DirectArgs& R, int64_t first, int n, void* mem) {
+__device__ __forceinline__ const int32_t* sort_chunk(const DirectArgs& R, int64_t first, int n,
+                                                     void* mem) {
   int size = 1;
   while (size < n) size <<= 1;
   int64_t* key = static_cast<int64_t*>(mem);
@@ -586,9 +587,9 @@ __device__ __forceinline__ void each_digit(const DirectArgs& R, const UnitDigits
 //
 // What bounds it: VALU issue and the latency of the chain row -> columns ->
 // cell -> result slot, not bytes (the vector units are busy 60 % of the time,
-// the LDS 24 %, wavefronts wait 56 % of theirs).  Of 1.66 ms on 7,919 x 12,347 terms (9.8e7
-// products, 2.7 GB of result) the two walks alone take 0.94 ms, adding the
-// shared products 0.20, writing the others 0.54.  One workgroup of 1024
+// the LDS 24 %, wavefronts wait 56 % of theirs).  Of 1.66 ms on 7,919 x 12,347
+// terms (9.8e7 products, 2.7 GB of result) the two walks alone take 0.94 ms,
+// adding the shared products 0.20, writing the others 0.54.  One workgroup of 1024
 // threads per compute unit with 2^18 cells beats two of 512 with 2^17 (1.77
 // ms) and three of 512 with 2^16 (2.78 ms): a row is looked at once per
 // interval whatever it finds there.  A table that holds every product, with
